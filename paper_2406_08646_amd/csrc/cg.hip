@@ -47,6 +47,14 @@ __global__ void k_scal_reset(CgScalars* st, int32_t maxit) {
   }
 }
 
+// The state of a solve that the resident form handed back unsolved.
+__global__ void k_resume(CgScalars* st) {
+  if (threadIdx.x == 0 && blockIdx.x == 0) {
+    st->status = SPX_OK;
+    st->done = 0;
+  }
+}
+
 // dinv[r] = 1 / a_rr (and its fp32 rounding); a missing or zero diagonal
 // marks the run with SPX_ZERO_DIAGONAL.
 __global__ void k_dinv(int64_t n, const double* __restrict__ val, const int32_t* __restrict__ dpos,
@@ -704,7 +712,9 @@ int ensure_solver(spx_matrix* h, int nvec = 4) {
     SPX_CHECK_HIP(hipEventCreateWithFlags(&h->ev[1], hipEventDisableTiming));
   }
   // two sets of three partials (the pipelined form), four for the others
-  const int64_t cap = (int64_t)std::max(fused_blocks(h), vector_blocks(h)) * 6;
+  // or the resident solve's exchange slots
+  const int64_t cap = std::max<int64_t>(
+      (int64_t)std::max(fused_blocks(h), vector_blocks(h)) * 6, kGridSlotWords);
   if (h->partial_cap < cap) {
     dfree(h->partials);
     h->partials = nullptr;
@@ -1069,8 +1079,8 @@ int finish_solve(spx_matrix* h, const Work& w, const Op<double>& A, const double
                  double* relres_out);
 
 // The one-workgroup solve: forced by SPX_OPT_SMALL_SOLVE = 2, chosen by the
-// default 1 for systems of at most kOneAutoRows rows when no launch-shape
-// option, profiling, graph replay or the single-reduction form asks for the
+// default 1 for systems of at most kOneAutoRows rows that the resident solve
+// below leaves when no launch-shape option, profiling, graph replay or the single-reduction form asks for the
 // multi-workgroup kernels; either way only if a 256-row tile fits in 64 KB.
 constexpr int64_t kOneAutoRows = 2048;  // measured crossover with the launch-per-iteration path
 
@@ -1082,14 +1092,34 @@ constexpr int64_t kOneAutoRows = 2048;  // measured crossover with the launch-pe
 // for (the captured chunk is the textbook iteration), take the textbook form.
 constexpr int64_t kSrAutoNnz = 2000000;
 constexpr int64_t kOneLds = 150 * 1024;  // dynamic LDS of the lone workgroup
+bool plain_options(const spx_matrix* h) {
+  return h->lanes_opt == 0 && h->variant_opt == 0 && h->rows_opt == 0 && h->rows32_opt == 0 &&
+         h->fused_opt == 0 && h->vec_blocks_opt == 0 && h->pipe_opt == 0 && h->vec_opt == 0 &&
+         h->nt_opt == 1 && !h->profile && !h->graph_opt;
+}
 bool use_one_workgroup(const spx_matrix* h, const Csr& M) {
   if (h->small_opt == 0 || h->cg_variant >= 1) return false;
   if ((M.tile_nnz[3] + 8) * (int64_t)sizeof(double) > 64 * 1024) return false;  // 256-row tiles fit
   if (h->small_opt == 2) return true;
-  const bool shape_default = h->lanes_opt == 0 && h->variant_opt == 0 && h->rows_opt == 0 &&
-                             h->rows32_opt == 0 && h->fused_opt == 0 && h->vec_blocks_opt == 0 &&
-                             h->pipe_opt == 0 && h->vec_opt == 0 && h->nt_opt == 1;
-  return shape_default && !h->profile && !h->graph_opt && M.n <= kOneAutoRows;
+  return plain_options(h) && M.n <= kOneAutoRows;
+}
+
+// The resident solve (cg_grid.hip): any fp32 inner solve, and fp64 systems
+// above kGridFromRows, whose matrix fits the CUs' LDS, when no option asks
+// for a launch shape or another form of the recurrences than its own, the
+// single reduction.  Per fp64 iteration,
+// resident against what took the size before: 121 rows 5.8 us against 5.5
+// (one workgroup), 289 rows 5.0 / 5.5, 1,089 rows 4.7 / 9.8, 2,025 rows 4.8
+// / 13.1; 4,225 rows 5.0 / 13.5 (two launches), 66,049 rows 6.8 / 13.9,
+// 117,649 rows of 27 entries 9.3 / 23.8, 409,600 rows of 5 9.2 / 26.1.  The
+// fp32 solve against three launches: 121 rows 8.7 / 27.5 us (with the
+// refinement's own work), 66,049 rows 6.9 / 16.1, 195,112 rows of 27
+// entries 11.8 / 27.6.
+constexpr int64_t kGridFromRows = 256;
+bool use_grid(const spx_matrix* h, const Csr& M, bool fp32) {
+  return h->small_opt == 1 &&
+         (fp32 || (h->cg_variant != 0 && h->cg_variant != 2 && M.n > kGridFromRows)) &&
+         plain_options(h) && grid_cg_fits(M, fp32);
 }
 
 }  // namespace
@@ -1119,6 +1149,18 @@ int cg_solve_impl(spx_matrix* h, const Work& w, const Csr& M, const double* b, d
   double* q = w.vec + 2 * n;
   CgScalars* st = w.scal;
   const unsigned G = (unsigned)fused_blocks(h);
+  if (use_grid(h, M, false)) {
+    bool launched = false;
+    SPX_TRY(launch_grid_cg(M, b, x, w.vec + 3 * n, w.partials, st, rtol, maxit, s, &launched));
+    if (launched) {
+      const int rc = finish_solve(h, w, A, b, x, st, s, iters_out, relres_out);
+      if (w.host[2].verify)
+        return set_error(SPX_HIP_ERROR, "cg_solve: the workgroups of the resident solve lost step");
+      if (w.host[2].status != kGridUnfit) return rc;
+      M.grid_unfit = true;  // the pattern's, kept with it: not tried again
+      clear_error();
+    }
+  }
   hipLaunchKernelGGL(k_scal_reset, dim3(1), dim3(64), 0, s, st, (int32_t)maxit);
   hipLaunchKernelGGL(k_dinv, dim3(grid1(n)), dim3(256), 0, s, n, M.val, M.dpos, w.dinv,
                      (float*)nullptr, st);
@@ -1357,8 +1399,27 @@ extern "C" int spx_cg_solve_mixed(spx_handle h, const double* b, double* x, doub
     }
     ++outer;
     CgScalars fin;
-    SPX_TRY(run_hs<float>(h, w, A32, d32, r32, p32, q32, h->dinv32, si, maxit_inner, check_every, s,
-                          &fin));
+    bool resident = false;
+    if (use_grid(h, M, true)) {
+      SPX_TRY(launch_grid_inner(M, d32, r32, p32, h->dinv32, w.partials, si, s, &resident));
+      if (resident) {
+        SPX_CHECK_HIP(hipMemcpyAsync(&w.host[3], si, sizeof(CgScalars), hipMemcpyDeviceToHost, s));
+        SPX_CHECK_HIP(hipStreamSynchronize(s));
+        fin = w.host[3];
+        if (fin.verify)
+          return set_error(SPX_HIP_ERROR,
+                           "cg_solve_mixed: the workgroups of the resident solve lost step");
+        if (fin.status == kGridUnfit) {
+          // the pattern's, kept with it; the launches below take this solve
+          M.grid_unfit32 = true;
+          resident = false;
+          hipLaunchKernelGGL(k_resume, dim3(1), dim3(64), 0, s, si);
+        }
+      }
+    }
+    if (!resident)
+      SPX_TRY(run_hs<float>(h, w, A32, d32, r32, p32, q32, h->dinv32, si, maxit_inner, check_every,
+                            s, &fin));
     inner += fin.iters;
     hipLaunchKernelGGL(k_ir_update, dim3(G), dim3(kBlock), 0, s, n, x, d32);
     if (fin.status == SPX_BREAKDOWN) {

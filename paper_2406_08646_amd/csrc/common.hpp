@@ -133,6 +133,8 @@ struct Csr {
   int64_t tile_nnz[4] = {0, 0, 0, 0};
   Window win;  // empty (lcol == nullptr) when the pattern does not profit from one
   RowSet rs;   // built on the first 16-column product
+  // the pattern's rows do not fit the resident solve's LDS (cg_grid.hip)
+  mutable bool grid_unfit = false, grid_unfit32 = false;
 };
 
 inline WinView win_view(const Csr& A) { return WinView{A.win.lcol, A.win.ptr, A.win.blk}; }
@@ -271,6 +273,22 @@ int launch_spmm(const Csr& A, int64_t nrhs, const double* X, int64_t ldx, double
 // stages each tile's rows of X in LDS (X and Y contiguous, 16-byte aligned)
 int build_rowset(Csr& A, int rows, hipStream_t s);
 int launch_spmm_rowset(const Csr& A, const double* X, double* Y, hipStream_t s);
+// cg_grid.hip: a whole CG solve as one cooperative launch.  grid_cg_fits:
+// the pattern may take it.  launch_grid_cg: the fp64 solve with the work
+// vector u[n]; resets *st.  launch_grid_inner: the fp32 inner solve of the
+// refinement, from the state k_ir_finish left in *st.  slots: kGridSlotWords
+// 8-byte words.  *launched is false when the device refused the launch.
+// Besides the solver's statuses st->status may come back as kGridUnfit
+// (nothing solved, no vector changed), and st->verify as 1 when a wait
+// between workgroups gave up.
+constexpr int kGridSlotWords = 16384;
+constexpr int32_t kGridUnfit = 1;
+constexpr int32_t kGridTimedOut = 2;
+bool grid_cg_fits(const Csr& M, bool fp32);
+int launch_grid_cg(const Csr& M, const double* b, double* x, double* u, double* slots,
+                   CgScalars* st, double rtol, int64_t maxit, hipStream_t s, bool* launched);
+int launch_grid_inner(const Csr& M, float* x, const float* r, float* z, const float* dinv,
+                      double* slots, CgScalars* st, hipStream_t s, bool* launched);
 // cg.hip
 int fused_blocks(const spx_matrix* h);
 int vector_blocks(const spx_matrix* h);
