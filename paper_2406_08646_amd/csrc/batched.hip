@@ -212,6 +212,31 @@ __global__ __launch_bounds__(BLOCK) void k_b_cg_persistent(
   }
 }
 
+// The same with each system's matrix and vectors in the compute unit
+// (cg_solve_regs: systems of at most BLOCK * RPT rows of at most K entries).
+template <int BLOCK, int H, int RPT, int K, bool LDSV>
+__global__ __launch_bounds__(BLOCK) void k_b_cg_regs(const BatchSys* __restrict__ sys, int nsys,
+                                                     int32_t* __restrict__ queue,
+                                                     const double* __restrict__ bvec,
+                                                     double* __restrict__ x, CgScalars* st,
+                                                     double rtol) {
+  extern __shared__ __align__(16) char smem[];
+  __shared__ double lds[6 * H * (BLOCK / 64)];
+  __shared__ int32_t pick;
+  for (;;) {
+    if (threadIdx.x == 0) pick = atomicAdd(queue, 1);
+    __syncthreads();
+    const int32_t k = pick;
+    if (k >= nsys) break;
+    const int s = queue[1 + k];
+    const BatchSys S = sys[s];
+    one::cg_solve_regs<BLOCK, H, RPT, K, LDSV>((int32_t)S.n, S.rowptr, S.col, S.val, S.dpos,
+                                            bvec + S.off, x + S.off, st[s].maxit, rtol, st + s,
+                                            reinterpret_cast<double*>(smem), lds);
+    __syncthreads();  // `pick` read by every thread before thread 0 rewrites it
+  }
+}
+
 }  // namespace
 }  // namespace spx
 
@@ -232,6 +257,57 @@ int launch_persistent(spx_batch* B, const PersistShape& ps, const double* bvec, 
   hipLaunchKernelGGL((k_b_cg_persistent<BLOCK, ROWS>), dim3((unsigned)G), dim3(BLOCK), ps.lds, s,
                      B->d_sys, B->nsys, B->d_queue, bvec, x, r, p, q, dinv, B->d_st, rtol);
   return SPX_OK;
+}
+
+template <int BLOCK, int H, int RPT, int K, bool LDSV>
+int launch_regs(spx_batch* B, const double* bvec, double* x, double rtol, hipStream_t s) {
+  const void* fn = reinterpret_cast<const void*>(&k_b_cg_regs<BLOCK, H, RPT, K, LDSV>);
+  constexpr size_t lds = (size_t)(LDSV ? 3 : 1) * BLOCK * RPT * sizeof(double);
+  if (lds > 64 * 1024)
+    SPX_CHECK_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  int fit = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&fit, fn, BLOCK, lds) != hipSuccess || fit < 1)
+    fit = 1;
+  const int G = (int)std::min<int64_t>(B->nsys, (int64_t)cu_count() * fit);
+  hipLaunchKernelGGL((k_b_cg_regs<BLOCK, H, RPT, K, LDSV>), dim3((unsigned)G), dim3(BLOCK), lds, s,
+                     B->d_sys, B->nsys, B->d_queue, bvec, x, B->d_st, rtol);
+  return SPX_OK;
+}
+
+// The persistent solve with the systems held in the compute units, where the
+// workgroup's tiles are as tall as it is (so that the dots add the rows in
+// the same order) and the largest system and longest row fit its registers.
+// Returns false when they do not.  512 threads stand for 1024: with 256
+// registers each (eight rows of seven entries, or twelve of five with x and
+// D^-1 in LDS) the compiler keeps the matrix there, with 128 it spilled it.
+// Longer rows at that size have shorter tiles.
+bool regs_persistent(spx_batch* B, const PersistShape& ps, const double* bvec, double* x,
+                     double rtol, hipStream_t s, int* status) {
+  if (ps.rows != ps.block) return false;
+  int64_t max_n = 0;
+  for (const BatchSys& S : B->sys) max_n = std::max(max_n, S.n);
+  const int64_t K = B->max_row;
+  if (ps.block == 256) {
+    if (max_n > 1024) return false;
+    if (K <= 5)
+      *status = launch_regs<256, 1, 4, 5, false>(B, bvec, x, rtol, s);
+    else if (K <= 9)
+      *status = launch_regs<256, 1, 4, 9, false>(B, bvec, x, rtol, s);
+    else if (K <= 27)
+      *status = launch_regs<256, 1, 4, 27, false>(B, bvec, x, rtol, s);
+    else
+      return false;
+    return true;
+  }
+  if (K <= 5 && max_n <= 4096)
+    *status = launch_regs<512, 2, 8, 5, false>(B, bvec, x, rtol, s);
+  else if (K <= 7 && max_n <= 4096)
+    *status = launch_regs<512, 2, 8, 7, false>(B, bvec, x, rtol, s);
+  else if (K <= 5 && max_n <= 6144)
+    *status = launch_regs<512, 2, 12, 5, true>(B, bvec, x, rtol, s);
+  else
+    return false;
+  return true;
 }
 }  // namespace
 
@@ -358,7 +434,10 @@ extern "C" int spx_batch_cg(spx_batch_handle B, const double* bvec, double* x, d
     hipLaunchKernelGGL(k_b_reset, dim3((unsigned)ceil_div(ns, 64)), dim3(64), 0, s, B->d_st, ns,
                        (int32_t)maxit);
     hipLaunchKernelGGL(k_b_queue_reset, dim3(1), dim3(64), 0, s, B->d_queue);
-    if (ps.block == 256)
+    int held = SPX_OK;
+    if (regs_persistent(B, ps, bvec, x, rtol, s, &held))
+      SPX_TRY(held);
+    else if (ps.block == 256)
       SPX_TRY((launch_persistent<256, 256>(B, ps, bvec, x, r, p, q, dinv, rtol, s)));
     else if (ps.rows == 1024)
       SPX_TRY((launch_persistent<1024, 1024>(B, ps, bvec, x, r, p, q, dinv, rtol, s)));
