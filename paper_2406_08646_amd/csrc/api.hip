@@ -101,14 +101,16 @@ int cu_count() {
 }
 
 static void free_csr(Csr& M) {
-  dfree(M.rowptr);
-  dfree(M.col);
-  dfree(M.val);
+  if (M.block) {
+    dfree(M.block);
+  } else {
+    dfree(M.rowptr);
+    dfree(M.col);
+    dfree(M.val);
+    dfree(M.dpos);
+  }
   dfree(M.val32);
-  dfree(M.dpos);
-  dfree(M.win.lcol);
-  dfree(M.win.ptr);
-  dfree(M.win.blk);
+  window_release(&M.win);
   dfree(M.rs.col);
   dfree(M.rs.lidx);
   M = Csr();
@@ -124,9 +126,9 @@ extern "C" int spx_destroy(spx_handle h) {
   int cur = 0;
   (void)hipGetDevice(&cur);
   if (cur != h->device) (void)hipSetDevice(h->device);
+  if (!h->A.block) dfree(h->jmap);
   free_csr(h->A);
   free_csr(h->At);
-  dfree(h->jmap);
   dfree(h->perm);
   dfree(h->tmap);
   dfree(h->kslot);

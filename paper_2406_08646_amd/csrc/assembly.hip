@@ -15,6 +15,9 @@ namespace {
 constexpr int kBlock = 256;
 constexpr int kIpt = 8;
 constexpr int64_t kTile = kBlock * kIpt;
+// Tile of the row stage: the items it starts from and the most it holds.
+constexpr int64_t kRowTile = 512;  // 1024 measured slower (5.55 vs 5.3 ms at 131M items)
+constexpr int kRowCap = 1024;
 
 __device__ __forceinline__ uint32_t block_exscan(uint32_t v, uint32_t* lds_wave, uint32_t* total) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -43,48 +46,150 @@ __global__ void k_fill_i32(int32_t* p, int64_t count, int32_t value) {
   if (t < count) p[t] = value;
 }
 
-__global__ void k_fill_u32_local(uint32_t* p, int64_t count, uint32_t value) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t < count) p[t] = value;
-}
-
 __global__ void k_fill_f64(double* p, int64_t count, double value) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (t < count) p[t] = value;
 }
 
-__global__ void k_iota_u32(uint32_t* p, int64_t count) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t < count) p[t] = (uint32_t)t;
+// Triplets k .. k + kIpt of p (those at ncoo and beyond -1): two 16-byte
+// loads where p is aligned and the range whole.
+typedef int32_t int4v __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void load_ipt(const int32_t* __restrict__ p, int64_t k, int64_t ncoo,
+                                         bool aligned, int32_t (&a)[kIpt]) {
+  static_assert(kIpt == 8, "two vectors");
+  if (aligned && k + kIpt <= ncoo) {
+    const int4v x = *reinterpret_cast<const int4v*>(p + k);
+    const int4v y = *reinterpret_cast<const int4v*>(p + k + 4);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      a[u] = x[u];
+      a[4 + u] = y[u];
+    }
+  } else {
+#pragma unroll
+    for (int u = 0; u < kIpt; ++u) a[u] = k + u < ncoo ? p[k + u] : -1;
+  }
 }
 
-// Per tile of kTile triplets: number of kept triplets; flags indices >= n.
+// The row before triplet k, given this thread's rows from k on (k a
+// multiple of kIpt, threads in order): the lane before has it.
+__device__ __forceinline__ int32_t row_before(const int32_t* __restrict__ i, int64_t k,
+                                              int64_t ncoo, const int32_t (&a)[kIpt]) {
+  const int32_t up = __shfl_up(a[kIpt - 1], 1, 64);
+  return (threadIdx.x & 63) != 0 ? up : k > 0 && k < ncoo ? i[k - 1] : -1;
+}
+
+// Per tile of kTile triplets: number of kept triplets in cnt[tile] and of
+// triplets whose row differs from the one before in cnt[ntiles + tile] (the
+// runs of equal rows, when every triplet is kept); flags indices >= n.
 __global__ __launch_bounds__(kBlock) void k_coo_count(const int32_t* __restrict__ i,
                                                       const int32_t* __restrict__ j,
-                                                      int64_t ncoo, int64_t n,
-                                                      uint32_t* __restrict__ tilecnt,
+                                                      int64_t ncoo, int64_t n, int64_t ntiles,
+                                                      uint32_t* __restrict__ cnt,
                                                       int32_t* __restrict__ err) {
   __shared__ uint32_t lds[kBlock / 64];
-  const int64_t base = (int64_t)blockIdx.x * kTile;
-  uint32_t c = 0;
+  const int64_t k = (int64_t)blockIdx.x * kTile + (int64_t)threadIdx.x * kIpt;
+  const bool aligned = ((reinterpret_cast<uintptr_t>(i) | reinterpret_cast<uintptr_t>(j)) & 15) == 0;
+  int32_t a[kIpt], b[kIpt];
+  load_ipt(i, k, ncoo, aligned, a);
+  load_ipt(j, k, ncoo, aligned, b);
+  int32_t prev = row_before(i, k, ncoo, a);
+  uint32_t c = 0;  // kept in the low half, run starts in the high one
   bool bad = false;
 #pragma unroll
-  for (int s = 0; s < kIpt; ++s) {
-    const int64_t k = base + (int64_t)s * kBlock + threadIdx.x;
-    if (k < ncoo) {
-      const int32_t a = i[k], b = j[k];
-      if (a >= 0 && b >= 0) {
-        if (a >= n || b >= n)
-          bad = true;
-        else
-          ++c;
-      }
+  for (int u = 0; u < kIpt; ++u) {
+    if (a[u] >= 0 && b[u] >= 0) {
+      if (a[u] >= n || b[u] >= n)
+        bad = true;
+      else
+        ++c;
     }
+    if (k + u < ncoo && (k + u == 0 || prev != a[u])) c += 1u << 16;
+    prev = a[u];
   }
   if (bad) atomicOr(err, 1);
+  static_assert(kTile < (1 << 16), "both counts in one word");
   uint32_t tot;
   (void)block_exscan(c, lds, &tot);
-  if (threadIdx.x == 0) tilecnt[blockIdx.x] = tot;
+  if (threadIdx.x == 0) {
+    cnt[blockIdx.x] = tot & 0xffffu;
+    cnt[ntiles + blockIdx.x] = tot >> 16;
+  }
+}
+
+// The runs of equal rows in order: run r's row and first triplet (every
+// triplet kept).  off: the tiles' run starts, less base.
+__global__ __launch_bounds__(kBlock) void k_seg_emit(const int32_t* __restrict__ i, int64_t ncoo,
+                                                     const uint32_t* __restrict__ off,
+                                                     uint32_t base, uint32_t* __restrict__ row,
+                                                     uint32_t* __restrict__ start, int64_t nseg) {
+  __shared__ uint32_t lds[kBlock / 64];
+  const int64_t k = (int64_t)blockIdx.x * kTile + (int64_t)threadIdx.x * kIpt;
+  int32_t a[kIpt];
+  load_ipt(i, k, ncoo, (reinterpret_cast<uintptr_t>(i) & 15) == 0, a);
+  const int32_t before = row_before(i, k, ncoo, a);
+  uint32_t heads = 0;
+#pragma unroll
+  for (int u = 0; u < kIpt; ++u) {
+    const int32_t prev = u == 0 ? before : a[u > 0 ? u - 1 : 0];
+    if (k + u < ncoo && (k + u == 0 || prev != a[u])) heads |= 1u << u;
+  }
+  uint32_t at = off[blockIdx.x] - base + block_exscan(__popc(heads), lds, nullptr);
+#pragma unroll
+  for (int u = 0; u < kIpt; ++u) {
+    if (heads >> u & 1u) {
+      row[at] = (uint32_t)a[u];
+      start[at] = (uint32_t)(k + u);
+      ++at;
+    }
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) start[nseg] = (uint32_t)ncoo;
+}
+
+// Runs in sorted order: their first triplets and lengths.
+__global__ void k_seg_lengths(const uint32_t* __restrict__ order, const uint32_t* __restrict__ start,
+                              int64_t nseg, uint32_t* __restrict__ first,
+                              uint32_t* __restrict__ len) {
+  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= nseg) return;
+  const uint32_t r = order[e], a = start[r];
+  first[e] = a;
+  len[e] = start[r + 1] - a;
+}
+
+// tile[b] = the first run that starts a row and whose first item is at b
+// kRowTile or later, for b = 0 .. tiles (row: the runs' rows in order; SEG:
+// pos their first items, pos[count] the item count; else every item is a
+// run), with that run's first item.  The search stops kRowCap + 1 runs on: the rows of the tile before
+// then exceed a tile's capacity, wherever the next row starts.
+template <bool SEG>
+__global__ void k_row_tiles(const uint32_t* __restrict__ row, const uint32_t* __restrict__ pos,
+                            int64_t count, int64_t tiles, uint2* __restrict__ tile) {
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  int64_t lo, hi, e = t;
+  uint64_t heads = 0;
+  if constexpr (SEG) {  // a thread per run, the one past the last included
+    heads = __ballot(t >= count || t == 0 || row[t] != row[t - 1]);
+    if (t > count) return;
+    lo = t == 0 ? 0 : (int64_t)pos[t - 1] / kRowTile + 1;
+    hi = t == count ? tiles : (int64_t)pos[t] / kRowTile;
+    if (lo > hi) return;
+  } else {  // a thread per tile
+    if (t > tiles) return;
+    lo = hi = t;
+    e = t * kRowTile < count ? t * kRowTile : count;
+  }
+  const int64_t lim = e + kRowCap + 1 < count ? e + kRowCap + 1 : count;
+  if constexpr (SEG) {
+    // the next row start among this wave's runs, where there is one
+    const int lane = threadIdx.x & 63;
+    const uint64_t m = heads >> lane;
+    e += m ? __ffsll((unsigned long long)m) - 1 : 64 - lane;
+  }
+  while (e > 0 && e < lim && row[e] == row[e - 1]) ++e;
+  if (e > lim) e = lim;
+  const uint2 v = make_uint2((uint32_t)e, SEG ? pos[e] : (uint32_t)e);
+  for (int64_t b = lo; b <= hi; ++b) tile[b] = v;
 }
 
 // Stable compaction of the kept triplets into (key, k) pairs with
@@ -133,140 +238,273 @@ __global__ __launch_bounds__(kBlock) void k_coo_compact(const int32_t* __restric
   }
 }
 
-// Second stage of the two-stage order: the kept items sorted stably by row
+// Second stage of the two-stage order: runs of items sorted stably by row
 // alone (increasing k within a row) are re-sorted by column inside each row
 // in LDS, ties keeping their order, which gives the (row, column, k) order
-// of the full sort.  Tile b takes the whole rows whose first item lies in
-// [b kRowTile, (b + 1) kRowTile); when those rows hold more than kRowCap
-// items, *overflow is set and the caller sorts the full keys instead.
-// Output: key row << cb | col and k at the item's final position.
-constexpr int64_t kRowTile = 512;  // 1024 measured slower (5.55 vs 5.3 ms at 131M items)
-constexpr int kRowCap = 1024;
+// of the full sort.  Tile b takes the whole rows whose first run is one of
+// its runs (those that start in items [b kRowTile, (b + 1) kRowTile)); when
+// those rows hold more than kRowCap items, *overflow is set and the caller
+// sorts the full keys instead.
 constexpr int kRowPosBits = 10;  // positions in a tile, in the rank key
 static_assert(kRowCap <= (1 << kRowPosBits), "tile positions must fit the rank key");
 constexpr int kRowColBits = 32 - kRowPosBits;  // columns of the rank key (n up to 2^22)
 constexpr int kRowIpt = kRowCap / kBlock;  // items per thread
+typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
 
-// The tile's range [q0, q1): q0 is the first row start in [b0, end0) (end0
-// if none), q1 the first at or after end0, searched up to
-// lim1 = end0 + kRowCap + 1 (q1 = lim1 when none is found there, which is
-// more than kRowCap past any q0; q1 = count when lim1 reaches count).  Both
-// searches run in the same steps; every thread gets both answers.
-__device__ __forceinline__ void tile_rows(const uint32_t* __restrict__ rk, int64_t count,
-                                          int64_t b0, int64_t end0, unsigned long long* slot,
-                                          int64_t* q0, int64_t* q1) {
-  const int64_t lim1 = end0 + kRowCap + 1 < count ? end0 + kRowCap + 1 : count;
-  if (threadIdx.x == 0) {
-    slot[0] = (unsigned long long)end0;
-    slot[1] = (unsigned long long)lim1;
-  }
-  __syncthreads();
-  for (int64_t off = 0;; off += kBlock) {
-    const int64_t qa = b0 + off + threadIdx.x, qb = end0 + off + threadIdx.x;
-    if (qa < end0 && (qa == 0 || rk[qa] != rk[qa - 1])) atomicMin(&slot[0], (unsigned long long)qa);
-    if (qb < lim1 && rk[qb] != rk[qb - 1]) atomicMin(&slot[1], (unsigned long long)qb);
-    __syncthreads();
-    const bool done0 = slot[0] < (unsigned long long)end0 || b0 + off + kBlock >= end0;
-    const bool done1 = slot[1] < (unsigned long long)lim1 || end0 + off + kBlock >= lim1;
-    __syncthreads();
-    if (done0 && done1) break;
-  }
-  *q0 = (int64_t)slot[0];
-  *q1 = (int64_t)slot[1];
-}
+// What the row-tile stage reads and writes.  Runs in sorted order: row, the
+// first triplet (SEG) or the triplet itself (first), each tile's first run
+// and item (tile), and with SEG the runs' first items (pos, the item count
+// after the last).
+struct RowTiles {
+  const uint32_t* row;
+  const uint32_t* first;
+  const uint32_t* pos;
+  const uint2* tile;
+  const int32_t* j;
+  int32_t* perm;
+  // per tile, at its first item: its distinct entries' columns and first
+  // items, compact; how many, and where
+  uint32_t* ecol;
+  uint32_t* eq;
+  uint32_t* ecount;
+  uint32_t* eat;
+  // per row: its first entry in its tile, that tile, its diagonal entry
+  uint32_t* rent;
+  uint32_t* rtile;
+  int32_t* rdiag;
+  uint32_t* overflow;
+};
 
-// The tile's rows are found with one block-wide scan: item l starts a row
-// when its row key differs from item l - 1's; the inclusive count of starts
-// numbers the rows, and each start records its position, so an item's row
-// spans [start[row], start[row + 1]).  Its rank there is the number of the
-// row's items with a smaller column, or an equal column and a smaller
-// position (the row sort left equal columns in increasing k): one compare
-// of col << kRowPosBits | position.  Thread t
-// loads and ranks items t, t + kBlock, ...; the row numbering walks
-// contiguous runs of kRowIpt items per thread.
-__global__ __launch_bounds__(kBlock) void k_rowtile_sort(const uint32_t* __restrict__ rk,
-                                                         const uint32_t* __restrict__ rv,
-                                                         int64_t count,
-                                                         const int32_t* __restrict__ j, int cb,
-                                                         uint64_t* __restrict__ okeys,
-                                                         uint32_t* __restrict__ ovals,
-                                                         uint32_t* __restrict__ overflow) {
-  __shared__ uint32_t srow[kRowCap];
-  __shared__ uint32_t scol[kRowCap];
-  __shared__ int32_t start[kRowCap + 1];
-  __shared__ int16_t srid[kRowCap];
-  __shared__ uint32_t wtot[kBlock / 64];
-  __shared__ unsigned long long slot[2];
-  const int64_t b0 = (int64_t)blockIdx.x * kRowTile;
-  const int64_t end0 = b0 + kRowTile < count ? b0 + kRowTile : count;
-  int64_t q0, q1;
-  tile_rows(rk, count, b0, end0, slot, &q0, &q1);
-  if (q0 >= end0) return;  // no row starts here
-  if (q1 - q0 > kRowCap) {
-    if (threadIdx.x == 0) atomicOr(overflow, 1u);
+// The tile's rows and, once ranked, its distinct entries are numbered with
+// wave ballots.  An item's rank in its row is the number of the row's items
+// with a smaller column, or an equal column and a smaller position (the row
+// sort left equal columns in increasing k): one compare of col <<
+// kRowPosBits | position against every item of the row, 16 keys of LDS per
+// step.  These compares bound the kernel: 64 per item on the 3-D operator,
+// whose rows hold eight runs of eight.  SEG: the runs are longer than one
+// triplet, so the stage reads a few words per run and the columns of a run
+// as one piece; without it every item is its own run.
+template <bool SEG>
+__global__ __launch_bounds__(kBlock) void k_rowtile_sort(RowTiles t) {
+  constexpr int W = kBlock / 64;
+  // 16.5 KB: eight workgroups per CU, so that their chains of loads (tile,
+  // runs, columns) hide each other
+  __shared__ uint32_t first[kRowCap];              // run -> first triplet
+  __shared__ __align__(16) uint32_t key[kRowCap];  // item -> rank key, then in order
+  __shared__ uint16_t pre[SEG ? kRowCap : 1];      // run -> first item
+  __shared__ uint16_t run[SEG ? kRowCap : 1];      // item -> run
+  __shared__ uint16_t rid[kRowCap];                // run -> row of the tile
+  __shared__ uint16_t start[kRowCap + 1];          // row of the tile -> first item
+  __shared__ uint32_t count[2][kRowIpt * W];
+  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
+  const uint64_t below = (1ull << lane) - 1ull;
+  const int64_t b = blockIdx.x;
+  const uint2 ta = t.tile[b], tb = t.tile[b + 1];
+  const int64_t s0 = ta.x, s1 = tb.x, q0 = ta.y, items = (int64_t)tb.y - q0;
+  if (s0 >= s1) {  // no row starts here
+    if (tid == 0) t.ecount[b] = 0;
     return;
   }
-  const int L = (int)(q1 - q0);
-  uint32_t kv[kRowIpt];
-#pragma unroll
-  for (int u = 0; u < kRowIpt; ++u) {
-    const int l = threadIdx.x + u * kBlock;
-    if (l < L) {
-      kv[u] = rv[q0 + l];
-      srow[l] = rk[q0 + l];
+  if (s1 - s0 > kRowCap || items > kRowCap) {
+    if (tid == 0) {
+      t.ecount[b] = 0;
+      atomicOr(t.overflow, 1u);
     }
+    return;
   }
-#pragma unroll
-  for (int u = 0; u < kRowIpt; ++u) {
-    const int l = threadIdx.x + u * kBlock;
-    if (l < L) scol[l] = ((uint32_t)j[kv[u]] << kRowPosBits) | (uint32_t)l;
-  }
-  __syncthreads();
-  const int l0 = threadIdx.x * kRowIpt;
-  uint32_t heads = 0;
-#pragma unroll
-  for (int u = 0; u < kRowIpt; ++u) {
-    const int l = l0 + u;
-    if (l < L && (l == 0 || srow[l] != srow[l - 1])) ++heads;
-  }
-  uint32_t tot;
-  uint32_t run = block_exscan(heads, wtot, &tot);
-#pragma unroll
-  for (int u = 0; u < kRowIpt; ++u) {
-    const int l = l0 + u;
-    if (l < L) {
-      if (l == 0 || srow[l] != srow[l - 1]) {
-        start[run] = l;
-        ++run;
+  const int S = (int)(s1 - s0), L = (int)items;
+  // the runs, kBlock at a time: their rows numbered in order
+  int rows = 0;
+  for (int c = 0; c < S; c += kBlock) {
+    const int e = c + tid;
+    const bool in = e < S;
+    uint32_t row = 0, prev = 0, p = (uint32_t)e, q = (uint32_t)e + 1;
+    if (in) {
+      row = t.row[s0 + e];
+      prev = e > 0 ? t.row[s0 + e - 1] : 0;
+      first[e] = t.first[s0 + e];
+      if constexpr (SEG) {
+        p = (uint32_t)((int64_t)t.pos[s0 + e] - q0);
+        q = (uint32_t)((int64_t)t.pos[s0 + e + 1] - q0);
       }
-      srid[l] = (int16_t)(run - 1);
+    }
+    const bool head = in && (e == 0 || row != prev);
+    const uint64_t m = __ballot(head);
+    uint32_t* slot = count[(c / kBlock) & 1];
+    if (lane == 0) slot[w] = (uint32_t)__popcll(m);
+    __syncthreads();
+    int r = rows + (int)__popcll(m & below);
+#pragma unroll
+    for (int ww = 0; ww < W; ++ww) {
+      if (ww < w) r += (int)slot[ww];
+      rows += (int)slot[ww];
+    }
+    if (in) {
+      if (head) start[r] = (uint16_t)p;
+      rid[e] = (uint16_t)(head ? r : r - 1);
+      if constexpr (SEG) {
+        pre[e] = (uint16_t)p;
+        for (uint32_t l = p; l < q; ++l) run[l] = (uint16_t)e;
+      }
     }
   }
-  if (threadIdx.x == 0) start[tot] = L;
+  if (tid == 0) start[rows] = (uint16_t)L;
   __syncthreads();
+  // the triplet of item l
+  auto triplet = [&](int l) -> uint32_t {
+    if constexpr (SEG) {
+      const int e = run[l];
+      return first[e] + (uint32_t)(l - pre[e]);
+    } else {
+      return first[l];
+    }
+  };
 #pragma unroll
   for (int u = 0; u < kRowIpt; ++u) {
-    const int l = threadIdx.x + u * kBlock;
+    const int l = tid + u * kBlock;
+    if (l < L) key[l] = ((uint32_t)t.j[triplet(l)] << kRowPosBits) | (uint32_t)l;
+  }
+  __syncthreads();
+  uint32_t k4[kRowIpt];
+  int at4[kRowIpt];
+#pragma unroll
+  for (int u = 0; u < kRowIpt; ++u) {
+    const int l = tid + u * kBlock;
+    k4[u] = 0;
+    at4[u] = 0;
     if (l < L) {
-      const int rid = srid[l];
-      const int rs = start[rid], re = start[rid + 1];
-      const uint32_t key = scol[l];
-      int rank = 0;
-      // sixteen keys per step, their loads issued together
-      int m = rs;
+      const int row = rid[SEG ? run[l] : l];
+      const int rs = start[row], re = start[row + 1];
+      const uint32_t k = key[l];
+      int at = rs, m = rs;
+      for (; m < re && (m & 3); ++m) at += key[m] < k ? 1 : 0;
       for (; m + 16 <= re; m += 16) {
-        uint32_t km[16];
+        uint4v km[4];
 #pragma unroll
-        for (int u = 0; u < 16; ++u) km[u] = scol[m + u];
+        for (int v = 0; v < 4; ++v) km[v] = *reinterpret_cast<const uint4v*>(key + m + 4 * v);
 #pragma unroll
-        for (int u = 0; u < 16; ++u) rank += km[u] < key ? 1 : 0;
+        for (int v = 0; v < 16; ++v) at += km[v / 4][v % 4] < k ? 1 : 0;
       }
-      for (; m < re; ++m) rank += scol[m] < key ? 1 : 0;
-      const int64_t at = q0 + rs + rank;
-      okeys[at] = ((uint64_t)srow[l] << cb) | (uint64_t)(key >> kRowPosBits);
-      ovals[at] = kv[u];
+      for (; m < re; ++m) at += key[m] < k ? 1 : 0;
+      k4[u] = k;
+      at4[u] = at;
     }
   }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < kRowIpt; ++u)
+    if (tid + u * kBlock < L) key[at4[u]] = k4[u];
+  __syncthreads();
+  // in order: the items' triplets, and the distinct entries numbered
+  uint64_t m4[kRowIpt];
+  bool first4[kRowIpt];
+#pragma unroll
+  for (int u = 0; u < kRowIpt; ++u) {
+    const int l = tid + u * kBlock;
+    bool head = false;
+    first4[u] = false;
+    if (l < L) {
+      const uint32_t k = key[l];
+      t.perm[q0 + l] = (int32_t)triplet((int)(k & (kRowCap - 1)));
+      first4[u] = l == start[rid[SEG ? run[l] : l]];
+      head = first4[u] || (key[l - 1] >> kRowPosBits) != (k >> kRowPosBits);
+    }
+    m4[u] = __ballot(head);
+    if (lane == 0) count[0][u * W + w] = (uint32_t)__popcll(m4[u]);
+  }
+  __syncthreads();
+  uint32_t before = 0;
+#pragma unroll
+  for (int u = 0; u < kRowIpt; ++u) {
+    uint32_t e = before + (uint32_t)__popcll(m4[u] & below);
+#pragma unroll
+    for (int ww = 0; ww < W; ++ww) {
+      const uint32_t x = count[0][u * W + ww];
+      if (ww < w) e += x;
+      before += x;
+    }
+    if (m4[u] >> lane & 1ull) {
+      const int l = tid + u * kBlock;
+      const int64_t r = s0 + (SEG ? run[l] : l);  // of the item's row: its first when first4
+      const uint32_t c = key[l] >> kRowPosBits, row = t.row[r];
+      t.ecol[q0 + e] = c;
+      t.eq[q0 + e] = (uint32_t)(q0 + l);
+      if (first4[u]) {
+        // this row, and the empty rows before it, start here
+        for (uint32_t rr = r > 0 ? t.row[r - 1] + 1 : 0; rr <= row; ++rr) {
+          t.rent[rr] = e;
+          t.rtile[rr] = (uint32_t)b;
+        }
+      }
+      if (c == row) t.rdiag[row] = (int32_t)e;
+    }
+  }
+  if (tid == 0) {
+    t.ecount[b] = before;
+    t.eat[b] = (uint32_t)q0;
+  }
+}
+
+// The tiles' entries to their final places: a wave per tile.
+__global__ __launch_bounds__(kBlock) void k_entries(const uint32_t* __restrict__ ecol,
+                                                    const uint32_t* __restrict__ eq,
+                                                    const uint32_t* __restrict__ off,
+                                                    const uint32_t* __restrict__ eat,
+                                                    int64_t tiles, int32_t* __restrict__ col,
+                                                    int32_t* __restrict__ jmap) {
+  const int64_t b = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
+  if (b >= tiles) return;
+  const uint32_t to = off[b], cnt = off[b + 1] - to;
+  if (cnt == 0) return;
+  const uint32_t from = eat[b];
+  constexpr int U = 4;  // loads in flight together
+  for (uint32_t e0 = threadIdx.x & 63; e0 < cnt; e0 += 64 * U) {
+    uint32_t c[U], q[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint32_t e = e0 + 64 * u < cnt ? e0 + 64 * u : cnt - 1;
+      c[u] = ecol[from + e];
+      q[u] = eq[from + e];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint32_t e = e0 + 64 * u;
+      if (e < cnt) {
+        col[to + e] = (int32_t)c[u];
+        jmap[to + e] = (int32_t)q[u];
+      }
+    }
+  }
+}
+
+// Per-row words of a new pattern: no entry, past the last tile, no diagonal;
+// and no entries past the last tile.
+__global__ void k_row_init(uint32_t* rent, uint32_t* rtile, int32_t* rdiag, int64_t n,
+                           uint32_t tiles, uint32_t* ecount) {
+  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (r == 0) ecount[tiles] = 0;
+  if (r >= n) return;
+  rent[r] = 0;
+  rtile[r] = tiles;
+  rdiag[r] = -1;
+}
+
+// rowptr and dpos from the rows' tiles; the closing jmap entry.
+__global__ void k_row_emit(const uint32_t* __restrict__ rent, const uint32_t* __restrict__ rtile,
+                           const int32_t* __restrict__ rdiag, const uint32_t* __restrict__ off,
+                           int64_t n, int64_t tiles, int64_t nvalid, int32_t* __restrict__ rowptr,
+                           int32_t* __restrict__ dpos, int32_t* __restrict__ jmap) {
+  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (r > n) return;
+  if (r == n) {
+    rowptr[n] = (int32_t)off[tiles];
+    jmap[off[tiles]] = (int32_t)nvalid;
+    return;
+  }
+  const uint32_t o = off[rtile[r]];
+  const int32_t d = rdiag[r];
+  rowptr[r] = (int32_t)(o + rent[r]);
+  dpos[r] = d >= 0 ? (int32_t)o + d : -1;
 }
 
 // Number of run heads (first element of each distinct key) per tile.
@@ -348,17 +586,41 @@ __global__ void k_rowptr_tail(const K* __restrict__ keys, int64_t count, int cb,
   if (r == 0 && jmap) jmap[nnz] = (int32_t)count;
 }
 
-// Longest row: wave max, then workgroup max in LDS, one atomic per workgroup.
-__global__ __launch_bounds__(256) void k_max_row(const int32_t* __restrict__ rowptr, int64_t n,
-                                                 int32_t* __restrict__ out) {
-  __shared__ int32_t wmax[4];
-  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  int32_t len = r < n ? rowptr[r + 1] - rowptr[r] : 0;
+// out[0] = longest row, out[1 + k] = most entries in a block of 32 << k
+// consecutive rows (k < 4).  At most kStatBlocks workgroups, each with its
+// own maxima before its atomics: one address for all of them (one atomic per
+// 256 rows took 96 us for 2M rows).
+constexpr int kStatBlocks = 256;
+__global__ __launch_bounds__(256) void k_row_stats(const int32_t* __restrict__ rowptr, int64_t n,
+                                                   int32_t* __restrict__ out) {
+  __shared__ int32_t lds[4][5];
+  int32_t m[5] = {0, 0, 0, 0, 0};
+  for (int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x; r < n; r += (int64_t)gridDim.x * 256) {
+    const int32_t p = rowptr[r];
+    m[0] = max(m[0], rowptr[r + 1] - p);
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) len = max(len, __shfl_xor(len, off, 64));
-  if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = len;
+    for (int k = 0; k < 4; ++k) {
+      const int64_t R = 32 << k;
+      if (r % R == 0) m[1 + k] = max(m[1 + k], rowptr[r + R < n ? r + R : n] - p);
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < 5; ++k) {
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) m[k] = max(m[k], __shfl_xor(m[k], off, 64));
+    if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6][k] = m[k];
+  }
   __syncthreads();
-  if (threadIdx.x == 0) atomicMax(out, max(max(wmax[0], wmax[1]), max(wmax[2], wmax[3])));
+  if (threadIdx.x < 5) {
+    const int k = threadIdx.x;
+    atomicMax(out + k, max(max(lds[0][k], lds[1][k]), max(lds[2][k], lds[3][k])));
+  }
+}
+
+void launch_row_stats(const Csr& M, int64_t n, int32_t* out, hipStream_t s) {
+  const int64_t g = std::min<int64_t>(ceil_div(n, 256), kStatBlocks);
+  hipLaunchKernelGGL(k_row_stats, dim3((unsigned)std::max<int64_t>(g, 1)), dim3(256), 0, s, M.rowptr,
+                     n, out);
 }
 
 // Tiled numeric stage: a workgroup owns `ents` consecutive entries.
@@ -506,162 +768,289 @@ inline unsigned grid_for(int64_t count, int block) {
   return (unsigned)std::max<int64_t>(1, ceil_div(count, block));
 }
 
-template <typename K>
-int symbolic(spx_matrix* h, const int32_t* i, const int32_t* j, hipStream_t s) {
-  const int64_t n = h->n, ncoo = h->ncoo;
+void set_row_stats(Csr& M, const int32_t* v) {
+  M.max_row = v[0];
+  for (int k = 0; k < 4; ++k) M.tile_nnz[k] = v[1 + k];
+}
+
+// Device buffers of one preallocation, freed once the stream has passed it.
+struct Scratch {
+  hipStream_t s;
+  void* p[4] = {};
+  int n = 0;
+  explicit Scratch(hipStream_t stream) : s(stream) {}
+  Scratch(const Scratch&) = delete;
+  Scratch& operator=(const Scratch&) = delete;
+  template <typename T>
+  int get(T** out, size_t count) {
+    if (n == 4) return set_error(SPX_HIP_ERROR, "coo_preallocate: too many buffers");
+    SPX_TRY(dalloc_n(out, count));
+    p[n++] = *out;
+    return SPX_OK;
+  }
+  ~Scratch() {
+    if (n > 0) (void)hipStreamSynchronize(s);
+    for (int k = 0; k < n; ++k) dfree(p[k]);
+  }
+};
+
+// Parts of one buffer of 32-bit words, each aligned for 16-byte loads.
+struct Parts {
+  int64_t words = 0;
+  int64_t take(int64_t count) {
+    const int64_t at = words;
+    words += (count + 15) & ~int64_t(15);
+    return at;
+  }
+};
+
+// The counts' words in misc: an index out of range, kept triplets, kept
+// triplets and runs of equal rows together, a row tile that overflowed,
+// entries, the row statistics, the window index's statistics.
+enum { kErr = 0, kKept = 1, kBoth = 2, kOver = 3, kNnz = 4, kStats = 5, kWin = 10, kMisc = 16 };
+static_assert(kWin % 2 == 0 && kWin + kWinStats <= kMisc, "misc holds the statistics");
+
+struct CooIn {
+  const int32_t* i;
+  const int32_t* j;
+  int64_t ntiles, nvalid, nruns;
+  uint32_t* misc;
+  const uint32_t* tileoff;  // kept triplets before each tile, then runs (less nvalid)
+};
+
+int read_misc(const uint32_t* misc, uint32_t* host, hipStream_t s) {
+  SPX_CHECK_HIP(hipMemcpyAsync(host, misc, kMisc * sizeof(uint32_t), hipMemcpyDeviceToHost, s));
+  SPX_CHECK_HIP(hipStreamSynchronize(s));
+  return SPX_OK;
+}
+
+// The pattern's arrays, in one block, for at most `most` entries, values 0;
+// every array has its 64 bytes of tail padding.
+int alloc_pattern(spx_matrix* h, int64_t most, hipStream_t s) {
+  const int64_t n = h->n;
+  Parts parts;
+  const int64_t pad = 16;
+  const int64_t o_val = parts.take(2 * most + pad), o_col = parts.take(most + pad),
+                o_jmap = parts.take(most + 1 + pad), o_row = parts.take(n + 1 + pad),
+                o_dpos = parts.take(n + pad);
+  int32_t* w = nullptr;
+  SPX_TRY(dalloc_n(&w, (size_t)parts.words));
+  h->A.block = w;
+  h->A.n = n;
+  h->A.val = reinterpret_cast<double*>(w + o_val);
+  h->A.col = w + o_col;
+  h->A.rowptr = w + o_row;
+  h->A.dpos = w + o_dpos;
+  h->jmap = w + o_jmap;
+  hipLaunchKernelGGL(k_fill_f64, dim3(grid_for(most, 256)), dim3(256), 0, s, h->A.val, most, 0.0);
+  return SPX_OK;
+}
+
+// The row statistics and the window index of the pattern in place (at most
+// `most` entries, unless misc's overflow is set), and misc read back.
+// scratch: window_scratch(n) words.  Waits for the stream.
+int finish_pattern(spx_matrix* h, int64_t most, uint32_t* misc, uint32_t* scratch, uint32_t* host,
+                   hipStream_t s) {
+  launch_row_stats(h->A, h->n, (int32_t*)(misc + kStats), s);
+  Window win;
+  int st = window_enqueue(h->A, most, misc + kOver, scratch, misc + kWin, s, &win);
+  if (st == SPX_OK) st = read_misc(misc, host, s);
+  if (st != SPX_OK || host[kOver]) {
+    window_release(&win);
+    return st;
+  }
+  h->A.nnz = host[kNnz];
+  set_row_stats(h->A, (const int32_t*)(host + kStats));
+  window_keep(h->A, host + kWin, &win);
+  return SPX_OK;
+}
+
+// The two-stage order (n up to 2^22): a stable sort by row alone (32-bit
+// keys, few passes), then each tile's whole rows ranked by column in LDS.
+// Finite-element and edge streams name the same row several times in a row;
+// when every triplet is kept and those runs are at least kSegRun long on
+// average, the runs are sorted instead of the triplets (the 3-D operator's
+// 131M triplets are 16.4M runs: 0.25 ms of sorting instead of 1.9).
+// *overflow: a tile's rows exceed it, and nothing was built.
+constexpr int64_t kSegRun = 2;
+// Up to here the pattern's block holds an entry per triplet (20 bytes each,
+// 5 MB at most), and the host waits for the device twice instead of three
+// times.
+constexpr int64_t kCountTriplets = 1 << 18;
+int symbolic_rows(spx_matrix* h, const CooIn& in, hipStream_t s, bool* overflow) {
+  const int64_t n = h->n, ncoo = h->ncoo, nvalid = in.nvalid;
   const int cb = h->colbits;
-  const int bits = 2 * cb;
-  const int64_t ntiles = std::max<int64_t>(1, ceil_div(ncoo, kTile));
-  // misc: [0] err, [1] nvalid, [2] nnz, [3] maxrow, [4] row-tile overflow
-  uint32_t* misc = nullptr;
-  uint32_t* tilecnt = nullptr;
+  const bool all_kept = nvalid == ncoo;
+  const bool seg = all_kept && nvalid > 0 && nvalid >= kSegRun * in.nruns;
+  const int64_t count = seg ? in.nruns : nvalid;
+  const int64_t tiles = std::max<int64_t>(1, ceil_div(nvalid, kRowTile));
+  Scratch mem(s);
+  Parts parts;
+  const int64_t o_key = parts.take(count), o_key2 = parts.take(count), o_val = parts.take(count),
+                o_val2 = parts.take(count);
+  const int64_t o_start = parts.take(seg ? count + 1 : 0), o_first = parts.take(seg ? count : 0),
+                o_pos = parts.take(seg ? count + 1 : 0), o_tile = parts.take(2 * (tiles + 1));
+  const int64_t o_ecol = parts.take(nvalid), o_eq = parts.take(nvalid);
+  const int64_t o_ecount = parts.take(tiles + 1), o_eat = parts.take(tiles);
+  const int64_t o_rent = parts.take(n), o_rtile = parts.take(n), o_rdiag = parts.take(n);
+  const int64_t o_work = parts.take(std::max({radix_sort_work(count, cb), scan_scratch_elems(count),
+                                              scan_scratch_elems(tiles + 1), window_scratch(n)}));
+  uint32_t* w = nullptr;
+  SPX_TRY(mem.get(&w, (size_t)parts.words));
+  int32_t* perm = nullptr;
+  SPX_TRY(mem.get(&perm, (size_t)std::max<int64_t>(nvalid, 1)));
+  uint32_t *work = w + o_work, *ecount = w + o_ecount;
+
+  RowTiles t{};
+  t.j = in.j;
+  t.perm = perm;
+  t.ecol = w + o_ecol;
+  t.eq = w + o_eq;
+  t.ecount = ecount;
+  t.eat = w + o_eat;
+  t.rent = w + o_rent;
+  t.rtile = w + o_rtile;
+  t.rdiag = (int32_t*)(w + o_rdiag);
+  t.overflow = in.misc + kOver;
+  uint2* tile = reinterpret_cast<uint2*>(w + o_tile);
+  t.tile = tile;
+  hipLaunchKernelGGL(k_row_init, dim3(grid_for(n, 256)), dim3(256), 0, s, t.rent, t.rtile, t.rdiag,
+                     n, (uint32_t)tiles, ecount);
+  uint32_t *row = nullptr, *order = nullptr;
+  if (seg) {
+    hipLaunchKernelGGL(k_seg_emit, dim3((unsigned)in.ntiles), dim3(kBlock), 0, s, in.i, ncoo,
+                       in.tileoff + in.ntiles, (uint32_t)nvalid, w + o_key, w + o_start, count);
+    SPX_TRY(radix_sort_pairs_u32(w + o_key, w + o_key2, w + o_val, w + o_val2, count, cb, work, s,
+                                 &row, &order, nullptr, true));
+    hipLaunchKernelGGL(k_seg_lengths, dim3(grid_for(count, 256)), dim3(256), 0, s, order,
+                       w + o_start, count, w + o_first, w + o_pos);
+    SPX_TRY(exclusive_scan_u32(w + o_pos, w + o_pos, count, w + o_pos + count, work, s));
+    hipLaunchKernelGGL(k_row_tiles<true>, dim3(grid_for(count + 1, 256)), dim3(256), 0, s, row,
+                       w + o_pos, count, tiles, tile);
+    t.row = row;
+    t.first = w + o_first;
+    t.pos = w + o_pos;
+    hipLaunchKernelGGL(k_rowtile_sort<true>, dim3((unsigned)tiles), dim3(kBlock), 0, s, t);
+  } else {
+    // with every triplet kept the sort reads the caller's rows and takes the
+    // triplet numbers as its values: no compaction
+    if (!all_kept)
+      hipLaunchKernelGGL((k_coo_compact<uint32_t, true>), dim3((unsigned)in.ntiles), dim3(kBlock), 0,
+                         s, in.i, in.j, ncoo, n, cb, in.tileoff, w + o_key, w + o_val);
+    SPX_TRY(radix_sort_pairs_u32(w + o_key, w + o_key2, w + o_val, w + o_val2, count, cb, work, s,
+                                 &row, &order,
+                                 all_kept ? reinterpret_cast<const uint32_t*>(in.i) : nullptr,
+                                 all_kept));
+    hipLaunchKernelGGL(k_row_tiles<false>, dim3(grid_for(tiles + 1, 256)), dim3(256), 0, s, row,
+                       (const uint32_t*)nullptr, count, tiles, tile);
+    t.row = row;
+    t.first = order;
+    hipLaunchKernelGGL(k_rowtile_sort<false>, dim3((unsigned)tiles), dim3(kBlock), 0, s, t);
+  }
+  SPX_TRY(exclusive_scan_u32(ecount, ecount, tiles + 1, in.misc + kNnz, work, s));
+  // small patterns take room for as many entries as triplets instead of
+  // waiting for the count
+  uint32_t host[kMisc];
+  int64_t most = nvalid;
+  if (nvalid > kCountTriplets) {
+    SPX_TRY(read_misc(in.misc, host, s));
+    *overflow = host[kOver] != 0;
+    if (*overflow) return SPX_OK;
+    most = host[kNnz];
+  }
+  SPX_TRY(alloc_pattern(h, most, s));
+  hipLaunchKernelGGL(k_entries, dim3(grid_for(tiles, kBlock / 64)), dim3(kBlock), 0, s, t.ecol, t.eq,
+                     ecount, t.eat, tiles, h->A.col, h->jmap);
+  hipLaunchKernelGGL(k_row_emit, dim3(grid_for(n + 1, 256)), dim3(256), 0, s, t.rent, t.rtile,
+                     t.rdiag, ecount, n, tiles, nvalid, h->A.rowptr, h->A.dpos, h->jmap);
+  SPX_TRY(finish_pattern(h, most, in.misc, work, host, s));
+  *overflow = host[kOver] != 0;
+  if (*overflow) {
+    dfree(h->A.block);
+    h->A = Csr();
+    h->jmap = nullptr;
+    return SPX_OK;
+  }
+  mem.n = 1;  // perm stays
+  h->perm = perm;
+  return SPX_OK;
+}
+
+// One sort on the full (row, column) keys.
+template <typename K>
+int symbolic_full(spx_matrix* h, const CooIn& in, hipStream_t s) {
+  const int64_t n = h->n, ncoo = h->ncoo, nvalid = in.nvalid;
+  const int cb = h->colbits;
+  const int64_t cap = std::max<int64_t>(nvalid, 1);
+  const int64_t vt = std::max<int64_t>(1, ceil_div(nvalid, kTile));
+  Scratch mem(s);
   K* keys = nullptr;
-  // two separate value buffers: the one the sort leaves its result in
-  // becomes perm as it is
-  uint32_t* vals = nullptr;
-  uint32_t* vals_alt = nullptr;
-  int st = SPX_OK;
-  uint32_t host_misc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  const int64_t scratch_n = scan_scratch_elems(ntiles);
-  if ((st = dalloc_n(&misc, 64)) != SPX_OK) return st;
-  if ((st = dalloc_n(&tilecnt, (size_t)(ntiles + scratch_n))) != SPX_OK) {
-    dfree(misc);
-    return st;
-  }
-  uint32_t* scratch = tilecnt + ntiles;
-  const int64_t cap = std::max<int64_t>(ncoo, 1);
-  if ((st = dalloc(reinterpret_cast<void**>(&keys), sizeof(K) * (size_t)cap * 2 + 64)) != SPX_OK ||
-      (st = dalloc_n(&vals, (size_t)cap)) != SPX_OK ||
-      (st = dalloc_n(&vals_alt, (size_t)cap)) != SPX_OK) {
-    dfree(keys);
-    dfree(vals);
-    dfree(tilecnt);
-    dfree(misc);
-    return st;
-  }
-  K* keys_alt = keys + cap;
+  uint32_t *vals = nullptr, *vals_alt = nullptr, *work = nullptr;
+  SPX_TRY(mem.get(&keys, (size_t)cap * 2));
+  SPX_TRY(mem.get(&work, (size_t)(vt + std::max({radix_sort_work(nvalid, 2 * cb),
+                                                 scan_scratch_elems(vt), window_scratch(n)}))));
+  SPX_TRY(mem.get(&vals, (size_t)cap));
+  SPX_TRY(mem.get(&vals_alt, (size_t)cap));
+  uint32_t* tilecnt = work;
+  work += vt;
   K* skeys = keys;
   uint32_t* svals = vals;
-  int64_t nvalid = 0, nnz = 0;
+  // (after an overflow misc holds the first attempt's counts)
+  hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, s, (int32_t*)in.misc + kOver,
+                     (int64_t)(kMisc - kOver), 0);
+  hipLaunchKernelGGL(k_coo_compact<K>, dim3((unsigned)in.ntiles), dim3(kBlock), 0, s, in.i, in.j,
+                     ncoo, n, cb, in.tileoff, keys, vals);
+  if constexpr (sizeof(K) == 8)
+    SPX_TRY(radix_sort_pairs_u64(keys, keys + cap, vals, vals_alt, nvalid, 2 * cb, work, s, &skeys,
+                                 &svals));
+  else
+    SPX_TRY(radix_sort_pairs_u32(keys, keys + cap, vals, vals_alt, nvalid, 2 * cb, work, s, &skeys,
+                                 &svals));
+  hipLaunchKernelGGL(k_heads_count<K>, dim3((unsigned)vt), dim3(kBlock), 0, s, skeys, nvalid,
+                     tilecnt);
+  SPX_TRY(exclusive_scan_u32(tilecnt, tilecnt, vt, in.misc + kNnz, work, s));
+  uint32_t host[kMisc];
+  SPX_TRY(read_misc(in.misc, host, s));
+  SPX_TRY(alloc_pattern(h, host[kNnz], s));
+  hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(n, 256)), dim3(256), 0, s, h->A.dpos, n, -1);
+  hipLaunchKernelGGL(k_heads_emit<K>, dim3((unsigned)vt), dim3(kBlock), 0, s, skeys, nvalid, cb,
+                     tilecnt, h->jmap, h->A.col, h->A.rowptr, h->A.dpos);
+  hipLaunchKernelGGL(k_rowptr_tail<K>, dim3(grid_for(n + 1, 256)), dim3(256), 0, s, skeys, nvalid,
+                     cb, n, in.misc + kNnz, h->A.rowptr, h->jmap);
+  SPX_TRY(finish_pattern(h, host[kNnz], in.misc, work, host, s));
+  // the sorted values are perm: that buffer stays
+  mem.n = 3;
+  if (svals == vals) mem.p[2] = vals_alt;
+  h->perm = reinterpret_cast<int32_t*>(svals);
+  return SPX_OK;
+}
 
-  do {
-    hipLaunchKernelGGL(k_fill_u32_local, dim3(1), dim3(64), 0, s, misc, (int64_t)64, 0u);
-    hipLaunchKernelGGL(k_coo_count, dim3((unsigned)ntiles), dim3(kBlock), 0, s, i, j, ncoo, n,
-                       tilecnt, (int32_t*)misc);
-    if ((st = exclusive_scan_u32(tilecnt, tilecnt, ntiles, misc + 1, scratch, s)) != SPX_OK) break;
-    // Keys wider than 32 bits take the two-stage order (up to 2^22 rows): a
-    // stable sort by row alone (32-bit keys, half the passes of the full
-    // key), then each tile's whole rows re-sorted by column in LDS.  The row keys and their
-    // alternate buffer live in the first half of `keys`; the full keys come
-    // out in the second half.
-    bool two_stage = sizeof(K) == 8 && cb <= kRowColBits;
-    if (hipMemcpyAsync(host_misc, misc, 8, hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess) {
-      st = set_error(SPX_HIP_ERROR, "coo_preallocate: %s", hipGetErrorString(hipGetLastError()));
-      break;
-    }
-    if (host_misc[0]) {
-      st = set_error(SPX_INDEX_OUT_OF_RANGE, "coo_preallocate: a COO index is >= n (%lld)",
+int symbolic(spx_matrix* h, const int32_t* i, const int32_t* j, hipStream_t s) {
+  const int64_t n = h->n, ncoo = h->ncoo;
+  const int64_t ntiles = std::max<int64_t>(1, ceil_div(ncoo, kTile));
+  Scratch mem(s);
+  uint32_t* misc = nullptr;
+  SPX_TRY(mem.get(&misc, (size_t)(kMisc + 2 * ntiles + scan_scratch_elems(2 * ntiles))));
+  uint32_t* cnt = misc + kMisc;
+  hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, s, (int32_t*)misc, (int64_t)kMisc, 0);
+  hipLaunchKernelGGL(k_coo_count, dim3((unsigned)ntiles), dim3(kBlock), 0, s, i, j, ncoo, n, ntiles,
+                     cnt, (int32_t*)misc + kErr);
+  SPX_TRY(exclusive_scan_u32(cnt, cnt, 2 * ntiles, misc + kBoth, cnt + 2 * ntiles, s, ntiles,
+                             misc + kKept));
+  uint32_t host[kMisc];
+  SPX_TRY(read_misc(misc, host, s));
+  if (host[kErr])
+    return set_error(SPX_INDEX_OUT_OF_RANGE, "coo_preallocate: a COO index is >= n (%lld)",
                      (long long)n);
-      break;
-    }
-    nvalid = host_misc[1];
-    // With every triplet kept the row sort reads the caller's rows and takes
-    // the triplet numbers as its values: no compaction.
-    const bool all_kept = nvalid == ncoo;
-    if (two_stage && !all_kept)
-      hipLaunchKernelGGL((k_coo_compact<uint32_t, true>), dim3((unsigned)ntiles), dim3(kBlock), 0,
-                         s, i, j, ncoo, n, cb, tilecnt, reinterpret_cast<uint32_t*>(keys), vals);
-    else if (!two_stage)
-      hipLaunchKernelGGL(k_coo_compact<K>, dim3((unsigned)ntiles), dim3(kBlock), 0, s, i, j, ncoo,
-                         n, cb, tilecnt, keys, vals);
-    if (two_stage) {
-      uint32_t* rk = reinterpret_cast<uint32_t*>(keys);
-      uint32_t *rk_out = nullptr, *rv_out = nullptr;
-      if ((st = radix_sort_pairs_u32(rk, rk + cap, vals, vals_alt, nvalid, cb, s, &rk_out, &rv_out,
-                                     all_kept ? reinterpret_cast<const uint32_t*>(i) : nullptr,
-                                     all_kept)) != SPX_OK)
-        break;
-      K* ok = keys + cap;
-      uint32_t* ov = rv_out == vals ? vals_alt : vals;
-      if (nvalid > 0)
-        hipLaunchKernelGGL(k_rowtile_sort, dim3((unsigned)ceil_div(nvalid, kRowTile)),
-                           dim3(kBlock), 0, s, rk_out, rv_out, nvalid, j, cb,
-                           reinterpret_cast<uint64_t*>(ok), ov, misc + 4);
-      if (hipMemcpyAsync(host_misc + 4, misc + 4, 4, hipMemcpyDeviceToHost, s) != hipSuccess ||
-          hipStreamSynchronize(s) != hipSuccess) {
-        st = set_error(SPX_HIP_ERROR, "coo_preallocate: %s", hipGetErrorString(hipGetLastError()));
-        break;
-      }
-      if (host_misc[4] == 0) {
-        skeys = ok;
-        svals = ov;
-      } else {
-        // rows too long for a tile: the full keys, compacted again
-        two_stage = false;
-        hipLaunchKernelGGL(k_coo_compact<K>, dim3((unsigned)ntiles), dim3(kBlock), 0, s, i, j,
-                           ncoo, n, cb, tilecnt, keys, vals);
-      }
-    }
-    if (!two_stage &&
-        (st = (sizeof(K) == 8
-                   ? radix_sort_pairs_u64((uint64_t*)keys, (uint64_t*)keys_alt, vals, vals_alt,
-                                          nvalid, bits, s, (uint64_t**)&skeys, &svals)
-                   : radix_sort_pairs_u32((uint32_t*)keys, (uint32_t*)keys_alt, vals, vals_alt,
-                                          nvalid, bits, s, (uint32_t**)&skeys, &svals))) != SPX_OK)
-      break;
-    const int64_t vt = std::max<int64_t>(1, ceil_div(nvalid, kTile));
-    hipLaunchKernelGGL(k_heads_count<K>, dim3((unsigned)vt), dim3(kBlock), 0, s, skeys, nvalid,
-                       tilecnt);
-    if ((st = exclusive_scan_u32(tilecnt, tilecnt, vt, misc + 2, scratch, s)) != SPX_OK) break;
-    if (hipMemcpyAsync(host_misc, misc, 16, hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess) {
-      st = set_error(SPX_HIP_ERROR, "coo_preallocate: %s", hipGetErrorString(hipGetLastError()));
-      break;
-    }
-    nnz = host_misc[2];
-    h->nvalid = nvalid;
-    h->A.n = n;
-    h->A.nnz = nnz;
-    if ((st = dalloc_n(&h->A.rowptr, (size_t)n + 1)) != SPX_OK) break;
-    if ((st = dalloc_n(&h->A.dpos, (size_t)n)) != SPX_OK) break;
-    if ((st = dalloc_n(&h->A.col, (size_t)std::max<int64_t>(nnz, 1))) != SPX_OK) break;
-    if ((st = dalloc_n(&h->A.val, (size_t)std::max<int64_t>(nnz, 1))) != SPX_OK) break;
-    if ((st = dalloc_n(&h->jmap, (size_t)nnz + 1)) != SPX_OK) break;
-    hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(n, 256)), dim3(256), 0, s, h->A.dpos, n, -1);
-    hipLaunchKernelGGL(k_fill_f64, dim3(grid_for(nnz, 256)), dim3(256), 0, s, h->A.val, nnz, 0.0);
-    hipLaunchKernelGGL(k_heads_emit<K>, dim3((unsigned)vt), dim3(kBlock), 0, s, skeys, nvalid, cb,
-                       tilecnt, h->jmap, h->A.col, h->A.rowptr, h->A.dpos);
-    hipLaunchKernelGGL(k_rowptr_tail<K>, dim3(grid_for(n + 1, 256)), dim3(256), 0, s, skeys,
-                       nvalid, cb, n, misc + 2, h->A.rowptr, h->jmap);
-    hipLaunchKernelGGL(k_max_row, dim3(grid_for(n, 256)), dim3(256), 0, s, h->A.rowptr, n,
-                       (int32_t*)(misc + 3));
-    // The sorted values are perm; keep that buffer, release the rest.
-    if (hipMemcpyAsync(host_misc, misc, 16, hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess) {
-      st = set_error(SPX_HIP_ERROR, "coo_preallocate: %s", hipGetErrorString(hipGetLastError()));
-      break;
-    }
-    h->A.max_row = host_misc[3];
-    if ((st = compute_tiles(h->A, s)) != SPX_OK) break;
-    if ((st = build_window(h->A, s)) != SPX_OK) break;
-    h->perm = reinterpret_cast<int32_t*>(svals);
-    if (svals == vals)
-      vals = nullptr;
-    else
-      vals_alt = nullptr;
-    if (hipStreamSynchronize(s) != hipSuccess) {
-      st = set_error(SPX_HIP_ERROR, "coo_preallocate: %s", hipGetErrorString(hipGetLastError()));
-      break;
-    }
-  } while (false);
-
-  dfree(keys);
-  dfree(vals);
-  dfree(vals_alt);
-  dfree(tilecnt);
-  dfree(misc);
-  return st;
+  const CooIn in{i, j, ntiles, host[kKept], (int64_t)host[kBoth] - host[kKept], misc, cnt};
+  h->nvalid = in.nvalid;
+  if (h->colbits <= kRowColBits) {
+    bool overflow = false;
+    SPX_TRY(symbolic_rows(h, in, s, &overflow));
+    if (!overflow) return SPX_OK;
+  }
+  return 2 * h->colbits <= 32 ? symbolic_full<uint32_t>(h, in, s)
+                              : symbolic_full<uint64_t>(h, in, s);
 }
 
 }  // namespace
@@ -669,30 +1058,28 @@ int symbolic(spx_matrix* h, const int32_t* i, const int32_t* j, hipStream_t s) {
 int ensure_transpose(spx_matrix* h, hipStream_t s) {
   const int64_t n = h->n, nnz = h->A.nnz;
   if (!h->has_t) {
-    uint32_t *keys = nullptr, *vals = nullptr;
-    int32_t* rowidx = nullptr;
     const int64_t cap = std::max<int64_t>(nnz, 1);
-    int st = SPX_OK;
-    do {
-      if ((st = dalloc_n(&keys, (size_t)cap * 2)) != SPX_OK) break;
-      if ((st = dalloc_n(&vals, (size_t)cap * 2)) != SPX_OK) break;
-      if ((st = dalloc_n(&rowidx, (size_t)cap)) != SPX_OK) break;
-      if ((st = dalloc_n(&h->At.rowptr, (size_t)n + 1)) != SPX_OK) break;
-      if ((st = dalloc_n(&h->At.col, (size_t)cap)) != SPX_OK) break;
-      if ((st = dalloc_n(&h->At.val, (size_t)cap)) != SPX_OK) break;
-      if ((st = dalloc_n(&h->At.dpos, (size_t)n)) != SPX_OK) break;
-      if ((st = dalloc_n(&h->tmap, (size_t)cap)) != SPX_OK) break;
+    {
+      Scratch mem(s);
+      Parts parts;
+      const int64_t o_key = parts.take(cap), o_key2 = parts.take(cap), o_val = parts.take(cap),
+                    o_val2 = parts.take(cap), o_row = parts.take(cap), o_stat = parts.take(kMisc),
+                    o_work = parts.take(std::max(radix_sort_work(nnz, h->colbits),
+                                                 window_scratch(n)));
+      uint32_t* w = nullptr;
+      SPX_TRY(mem.get(&w, (size_t)parts.words));
+      int32_t *rowidx = (int32_t*)(w + o_row), *stat = (int32_t*)(w + o_stat);
+      SPX_TRY(dalloc_n(&h->At.rowptr, (size_t)n + 1));
+      SPX_TRY(dalloc_n(&h->At.col, (size_t)cap));
+      SPX_TRY(dalloc_n(&h->At.val, (size_t)cap));
+      SPX_TRY(dalloc_n(&h->At.dpos, (size_t)n));
+      SPX_TRY(dalloc_n(&h->tmap, (size_t)cap));
       hipLaunchKernelGGL(k_expand_rows, dim3(grid_for(n, 256)), dim3(256), 0, s, h->A.rowptr, n,
                          rowidx);
-      if (nnz > 0) {
-        SPX_CHECK_HIP(hipMemcpyAsync(keys, h->A.col, sizeof(int32_t) * (size_t)nnz,
-                                     hipMemcpyDeviceToDevice, s));
-      }
-      hipLaunchKernelGGL(k_iota_u32, dim3(grid_for(nnz, 256)), dim3(256), 0, s, vals, nnz);
       uint32_t *sk = nullptr, *sv = nullptr;
-      if ((st = radix_sort_pairs_u32(keys, keys + cap, vals, vals + cap, nnz, h->colbits, s, &sk,
-                                     &sv)) != SPX_OK)
-        break;
+      SPX_TRY(radix_sort_pairs_u32(w + o_key, w + o_key2, w + o_val, w + o_val2, nnz, h->colbits,
+                                   w + o_work, s, &sk, &sv,
+                                   reinterpret_cast<const uint32_t*>(h->A.col), true));
       hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(n, 256)), dim3(256), 0, s, h->At.dpos, n, -1);
       hipLaunchKernelGGL(k_transpose_emit, dim3(grid_for(nnz, 256)), dim3(256), 0, s, sk, sv,
                          rowidx, nnz, h->At.rowptr, h->At.col, h->At.dpos);
@@ -701,24 +1088,21 @@ int ensure_transpose(spx_matrix* h, hipStream_t s) {
       if (nnz > 0)
         SPX_CHECK_HIP(hipMemcpyAsync(h->tmap, sv, sizeof(int32_t) * (size_t)nnz,
                                      hipMemcpyDeviceToDevice, s));
-      // row lengths of A^T
-      int32_t* mx = rowidx;  // reuse as scratch after the emit kernels
-      SPX_CHECK_HIP(hipStreamSynchronize(s));
-      hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, s, mx, (int64_t)1, 0);
-      hipLaunchKernelGGL(k_max_row, dim3(grid_for(n, 256)), dim3(256), 0, s, h->At.rowptr, n, mx);
-      int32_t host_mx = 0;
-      SPX_CHECK_HIP(hipMemcpyAsync(&host_mx, mx, 4, hipMemcpyDeviceToHost, s));
-      SPX_CHECK_HIP(hipStreamSynchronize(s));
-      h->At.max_row = host_mx;
+      hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, s, stat, (int64_t)kMisc, 0);
       h->At.n = n;
       h->At.nnz = nnz;
-      if ((st = compute_tiles(h->At, s)) != SPX_OK) break;
-      if ((st = build_window(h->At, s)) != SPX_OK) break;
-    } while (false);
-    dfree(keys);
-    dfree(vals);
-    dfree(rowidx);
-    if (st != SPX_OK) return st;
+      launch_row_stats(h->At, n, stat + kStats, s);
+      Window win;
+      uint32_t host[kMisc];
+      int st = window_enqueue(h->At, nnz, nullptr, w + o_work, (uint32_t*)stat + kWin, s, &win);
+      if (st == SPX_OK) st = read_misc((const uint32_t*)stat, host, s);
+      if (st != SPX_OK) {
+        window_release(&win);
+        return st;
+      }
+      set_row_stats(h->At, (const int32_t*)(host + kStats));
+      window_keep(h->At, host + kWin, &win);
+    }
     h->has_t = true;
     h->valT_fresh = false;
   }
@@ -775,7 +1159,7 @@ extern "C" int spx_coo_preallocate(int64_t n, int64_t ncoo, const int32_t* i, co
   int cb = 0;
   while (cb < 31 && ((int64_t)1 << cb) < n) ++cb;  // bits of n-1
   h->colbits = cb;
-  const int st = (2 * cb <= 32) ? symbolic<uint32_t>(h, i, j, s) : symbolic<uint64_t>(h, i, j, s);
+  const int st = symbolic(h, i, j, s);
   if (st != SPX_OK) {
     spx_destroy(h);
     return st;

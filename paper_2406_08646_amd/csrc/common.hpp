@@ -54,22 +54,26 @@ __host__ __device__ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + 
 // Stable LSD radix sort of (key, value) pairs by the low `bits` bits of the
 // key (1 <= bits <= 64).  Sorted output is returned in (*keys_out,
 // *vals_out), which point either at the input buffers or at the alternates.
-// All buffers hold `count` elements; scratch is allocated internally.
+// All buffers hold `count` elements; work: radix_sort_work(count, bits)
+// elements.  Asynchronous.
+int64_t radix_sort_work(int64_t count, int bits);
 int radix_sort_pairs_u64(uint64_t* keys, uint64_t* keys_alt, uint32_t* vals, uint32_t* vals_alt,
-                         int64_t count, int bits, hipStream_t s, uint64_t** keys_out,
-                         uint32_t** vals_out);
+                         int64_t count, int bits, uint32_t* work, hipStream_t s,
+                         uint64_t** keys_out, uint32_t** vals_out);
 // first_keys (optional): the first pass reads its keys there (keys is still
 // overwritten); iota_vals: the values are the item indices 0 .. count-1.
 int radix_sort_pairs_u32(uint32_t* keys, uint32_t* keys_alt, uint32_t* vals, uint32_t* vals_alt,
-                         int64_t count, int bits, hipStream_t s, uint32_t** keys_out,
-                         uint32_t** vals_out, const uint32_t* first_keys = nullptr,
-                         bool iota_vals = false);
+                         int64_t count, int bits, uint32_t* work, hipStream_t s,
+                         uint32_t** keys_out, uint32_t** vals_out,
+                         const uint32_t* first_keys = nullptr, bool iota_vals = false);
 
 // Exclusive scan of uint32 counts; out may alias in.  If total != nullptr
-// the sum is written there (device).  scratch: scan_scratch_elems(count).
+// the sum is written there (device), and the scan's value at index mid to
+// mid_out.  scratch: scan_scratch_elems(count).
 int64_t scan_scratch_elems(int64_t count);
 int exclusive_scan_u32(const uint32_t* in, uint32_t* out, int64_t count, uint32_t* total,
-                       uint32_t* scratch, hipStream_t s);
+                       uint32_t* scratch, hipStream_t s, int64_t mid = -1,
+                       uint32_t* mid_out = nullptr);
 
 // -------------------------------------------------------------- matrix
 // How products walk a matrix (chosen once per pattern, see spmv.hip).
@@ -93,6 +97,7 @@ constexpr int kWinBlock = 64;
 constexpr int kWinMaxBlocks = 64;
 constexpr int kWinSpan = 8192;
 struct Window {
+  void* block = nullptr;     // holds the three arrays
   uint16_t* lcol = nullptr;  // [nnz]
   int32_t* ptr = nullptr;    // [tiles + 1]: tile k's blocks are blk[ptr[k] .. ptr[k+1])
   int32_t* blk = nullptr;    // block numbers (x entries blk * kWinBlock ...)
@@ -123,6 +128,8 @@ struct WinView {
 
 struct Csr {
   int64_t n = 0, nnz = 0;
+  // holds rowptr, col, val and dpos (and the handle's jmap) when not null
+  void* block = nullptr;
   int32_t* rowptr = nullptr;
   int32_t* col = nullptr;
   double* val = nullptr;
@@ -248,9 +255,17 @@ int ensure_kslot(spx_matrix* h, hipStream_t s);
 int ensure_val32(spx_matrix* h, hipStream_t s);
 // spmv.hip
 int pick_lanes(const Csr& A, int opt);
-int compute_tiles(Csr& A, hipStream_t s);
-// window.hip
-int build_window(Csr& A, hipStream_t s);
+// window.hip: the window index of a pattern of at most `most` entries.
+// window_enqueue allocates *w (empty when there is no memory for it) and
+// enqueues its kernels, which do nothing once *off is set; scratch:
+// window_scratch(n) words; stats: kWinStats words, zero, 8-byte aligned.
+// window_keep, with stats read back, moves *w to A or releases it.
+constexpr int kWinStats = 6;
+int64_t window_scratch(int64_t n);
+int window_enqueue(const Csr& A, int64_t most, const uint32_t* off, uint32_t* scratch,
+                   uint32_t* stats, hipStream_t s, Window* w);
+void window_keep(Csr& A, const uint32_t* stats, Window* w);
+void window_release(Window* w);
 // assembly.hip: the numeric stage of h's pattern into out (nnz entries) in
 // mode (SPX_INSERT_VALUES or SPX_ADD_VALUES); h's own values are untouched
 int set_values_into(spx_handle h, const double* v, int mode, double* out, hipStream_t s);

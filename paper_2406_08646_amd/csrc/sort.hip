@@ -68,7 +68,8 @@ __global__ __launch_bounds__(kScanBlock) void k_scan_reduce(const uint32_t* __re
 __global__ __launch_bounds__(kScanBlock) void k_scan_apply(const uint32_t* in, uint32_t* out,
                                                            int64_t count,
                                                            const uint32_t* __restrict__ boff,
-                                                           uint32_t* __restrict__ total) {
+                                                           uint32_t* __restrict__ total, int64_t mid,
+                                                      uint32_t* __restrict__ mid_out) {
   __shared__ uint32_t lds[kScanBlock / 64];
   const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanIpt;
   uint32_t v[kScanIpt];
@@ -84,6 +85,7 @@ __global__ __launch_bounds__(kScanBlock) void k_scan_apply(const uint32_t* in, u
     if (base + k < count) {
       out[base + k] = run;
       if (total && base + k == count - 1) *total = run + v[k];
+      if (mid_out && base + k == mid) *mid_out = run;
     }
     run += v[k];
   }
@@ -92,6 +94,11 @@ __global__ __launch_bounds__(kScanBlock) void k_scan_apply(const uint32_t* in, u
 __global__ void k_fill_u32(uint32_t* p, int64_t count, uint32_t value) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (t < count) p[t] = value;
+}
+
+__global__ void k_iota(uint32_t* p, int64_t count) {
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (t < count) p[t] = (uint32_t)t;
 }
 
 // ------------------------------------------------------------ radix sort
@@ -232,39 +239,41 @@ __global__ __launch_bounds__(kSortBlock) void k_radix_scatter(
   }
 }
 
+// Bits of a digit when `bits` are sorted in as few passes as possible.
+inline int radix_digit_bits(int bits) {
+  const int passes = (bits + kMaxDigitBits - 1) / kMaxDigitBits;
+  return (bits + passes - 1) / passes;
+}
+
 // first_keys (optional): the first pass reads its keys there instead of in
 // keys, and with iota_vals its values are the item indices (vals is then
 // only written); keys and vals are overwritten either way.
 template <typename K>
 int radix_sort_impl(K* keys, K* keys_alt, uint32_t* vals, uint32_t* vals_alt, int64_t count,
-                    int bits, hipStream_t s, K** keys_out, uint32_t** vals_out,
+                    int bits, uint32_t* work, hipStream_t s, K** keys_out, uint32_t** vals_out,
                     const K* first_keys = nullptr, bool iota_vals = false) {
   *keys_out = keys;
   *vals_out = vals;
   if (count <= 1 || bits <= 0) {
-    if (first_keys || iota_vals) {
-      // nothing to order: the output is the input
-      if (count == 1 && first_keys)
-        SPX_CHECK_HIP(hipMemcpyAsync(keys, first_keys, sizeof(K), hipMemcpyDeviceToDevice, s));
-      if (count == 1 && iota_vals)
-        hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, s, vals, (int64_t)1, 0u);
-    }
+    // nothing to order: the output is the input
+    if (count >= 1 && first_keys)
+      SPX_CHECK_HIP(hipMemcpyAsync(keys, first_keys, sizeof(K) * (size_t)count,
+                                   hipMemcpyDeviceToDevice, s));
+    if (count >= 1 && iota_vals)
+      hipLaunchKernelGGL(k_iota, dim3((unsigned)ceil_div(count, 256)), dim3(256), 0, s, vals, count);
     return SPX_OK;
   }
   if (bits > (int)(8 * sizeof(K)))
     return set_error(SPX_INVALID_ARG, "radix sort: %d bits exceed the key width", bits);
-  const int passes = (bits + kMaxDigitBits - 1) / kMaxDigitBits;
-  const int dbits = (bits + passes - 1) / passes;
-  const int nb = 1 << dbits;
+  const int dbits = radix_digit_bits(bits);
+  const int passes = (bits + dbits - 1) / dbits;
   const int64_t ntiles = ceil_div(count, kSortTile);
-  const int64_t hist_n = (int64_t)nb * ntiles;
+  const int64_t hist_n = ((int64_t)1 << dbits) * ntiles;
   if (hist_n >= (int64_t)UINT32_MAX || count >= (int64_t)UINT32_MAX)
     return set_error(SPX_INVALID_ARG, "radix sort: %lld items is too many",
                      (long long)count);
-  uint32_t* hist = nullptr;
-  const int64_t scratch_n = scan_scratch_elems(hist_n);
-  SPX_TRY(dalloc_n(&hist, (size_t)(hist_n + scratch_n)));
-  uint32_t* scratch = hist + hist_n;
+  uint32_t* hist = work;
+  uint32_t* scratch = work + hist_n;
   // pass p reads (ck, cv) and writes (ak, av); with first_keys the first
   // pass reads the caller's keys and writes keys_alt, so the passes after
   // it alternate between keys_alt and keys
@@ -274,13 +283,11 @@ int radix_sort_impl(K* keys, K* keys_alt, uint32_t* vals, uint32_t* vals_alt, in
   uint32_t* av = vals_alt;
   K* next_k = keys;
   uint32_t* next_v = vals;
-  int st = SPX_OK;
-  for (int p = 0; p < passes && st == SPX_OK; ++p) {
+  for (int p = 0; p < passes; ++p) {
     const int shift = p * dbits;
     hipLaunchKernelGGL(k_radix_hist<K>, dim3((unsigned)ntiles), dim3(kSortBlock), 0, s, ck, count,
                        shift, dbits, hist, ntiles);
-    st = exclusive_scan_u32(hist, hist, hist_n, nullptr, scratch, s);
-    if (st != SPX_OK) break;
+    SPX_TRY(exclusive_scan_u32(hist, hist, hist_n, nullptr, scratch, s));
     hipLaunchKernelGGL(k_radix_scatter<K>, dim3((unsigned)ntiles), dim3(kSortBlock), 0, s, ck,
                        cv, ak, av, count, shift, dbits, hist, ntiles);
     // the buffer just written is the next input; the other one takes the
@@ -294,14 +301,7 @@ int radix_sort_impl(K* keys, K* keys_alt, uint32_t* vals, uint32_t* vals_alt, in
     ck = wk;
     cv = wv;
   }
-  hipError_t e = hipGetLastError();
-  // The free below waits for the passes; preallocation is synchronous.
-  hipError_t e2 = hipStreamSynchronize(s);
-  dfree(hist);
-  if (st != SPX_OK) return st;
-  if (e != hipSuccess) return set_error(SPX_HIP_ERROR, "radix sort launch: %s", hipGetErrorString(e));
-  if (e2 != hipSuccess)
-    return set_error(SPX_HIP_ERROR, "radix sort: %s", hipGetErrorString(e2));
+  SPX_CHECK_HIP(hipGetLastError());
   *keys_out = const_cast<K*>(ck);
   *vals_out = const_cast<uint32_t*>(cv);
   return SPX_OK;
@@ -320,7 +320,7 @@ int64_t scan_scratch_elems(int64_t count) {
 }
 
 int exclusive_scan_u32(const uint32_t* in, uint32_t* out, int64_t count, uint32_t* total,
-                       uint32_t* scratch, hipStream_t s) {
+                       uint32_t* scratch, hipStream_t s, int64_t mid, uint32_t* mid_out) {
   if (count <= 0) {
     if (total) hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, s, total, (int64_t)1, 0u);
     return SPX_OK;
@@ -328,7 +328,7 @@ int exclusive_scan_u32(const uint32_t* in, uint32_t* out, int64_t count, uint32_
   const int64_t nt = ceil_div(count, kScanTile);
   if (nt == 1) {
     hipLaunchKernelGGL(k_scan_apply, dim3(1), dim3(kScanBlock), 0, s, in, out, count,
-                       (const uint32_t*)nullptr, total);
+                       (const uint32_t*)nullptr, total, mid, mid_out);
     return SPX_OK;
   }
   uint32_t* bsum = scratch;
@@ -336,21 +336,28 @@ int exclusive_scan_u32(const uint32_t* in, uint32_t* out, int64_t count, uint32_
   hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)nt), dim3(kScanBlock), 0, s, in, count, bsum);
   SPX_TRY(exclusive_scan_u32(bsum, bsum, nt, nullptr, next, s));
   hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)nt), dim3(kScanBlock), 0, s, in, out, count,
-                     (const uint32_t*)bsum, total);
+                     (const uint32_t*)bsum, total, mid, mid_out);
   return SPX_OK;
 }
 
+int64_t radix_sort_work(int64_t count, int bits) {
+  if (count <= 1 || bits <= 0) return 0;
+  const int64_t hist_n = ((int64_t)1 << radix_digit_bits(bits)) * ceil_div(count, kSortTile);
+  return hist_n + scan_scratch_elems(hist_n);
+}
+
 int radix_sort_pairs_u64(uint64_t* keys, uint64_t* keys_alt, uint32_t* vals, uint32_t* vals_alt,
-                         int64_t count, int bits, hipStream_t s, uint64_t** keys_out,
-                         uint32_t** vals_out) {
-  return radix_sort_impl<uint64_t>(keys, keys_alt, vals, vals_alt, count, bits, s, keys_out,
+                         int64_t count, int bits, uint32_t* work, hipStream_t s,
+                         uint64_t** keys_out, uint32_t** vals_out) {
+  return radix_sort_impl<uint64_t>(keys, keys_alt, vals, vals_alt, count, bits, work, s, keys_out,
                                    vals_out);
 }
 
 int radix_sort_pairs_u32(uint32_t* keys, uint32_t* keys_alt, uint32_t* vals, uint32_t* vals_alt,
-                         int64_t count, int bits, hipStream_t s, uint32_t** keys_out,
-                         uint32_t** vals_out, const uint32_t* first_keys, bool iota_vals) {
-  return radix_sort_impl<uint32_t>(keys, keys_alt, vals, vals_alt, count, bits, s, keys_out,
+                         int64_t count, int bits, uint32_t* work, hipStream_t s,
+                         uint32_t** keys_out, uint32_t** vals_out, const uint32_t* first_keys,
+                         bool iota_vals) {
+  return radix_sort_impl<uint32_t>(keys, keys_alt, vals, vals_alt, count, bits, work, s, keys_out,
                                    vals_out, first_keys, iota_vals);
 }
 

@@ -78,11 +78,6 @@ __global__ __launch_bounds__(kWinRows) void k_spmv_window(int64_t n, const int32
   if (threadIdx.x < r1 - r0) y[r0 + threadIdx.x] = s;
 }
 
-__global__ void k_zero_i32(int32_t* p, int64_t count) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t < count) p[t] = 0;
-}
-
 // One tile per workgroup, its columns and values staged by direct loads.
 template <int BLOCK>
 __global__ __launch_bounds__(BLOCK) void k_spmv_dma(int64_t n, const int32_t* __restrict__ rowptr,
@@ -108,21 +103,6 @@ __global__ __launch_bounds__(BLOCK) void k_spmv_dma(int64_t n, const int32_t* __
   }
   dma_products<BLOCK, double, double, double>(x, t0, t1, lcol, lval);
   if (owner) y[r0 + threadIdx.x] = dma_row_sum<double, double>(lval, t0, rs, re);
-}
-
-// Largest entry count of any block of 32, 64, 128 and 256 consecutive rows.
-__global__ void k_tile_nnz(const int32_t* __restrict__ rowptr, int64_t n, int32_t* __restrict__ out) {
-  const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;  // index of a 32-row block
-  const int64_t nb32 = (n + 31) / 32;
-  if (b >= nb32) return;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const int64_t R = 32 << k;
-    if ((b * 32) % R != 0) continue;
-    const int64_t r0 = b * 32;
-    const int64_t r1 = r0 + R < n ? r0 + R : n;
-    atomicMax(&out[k], rowptr[r1] - rowptr[r0]);
-  }
 }
 
 template <int L, bool NT>
@@ -467,23 +447,6 @@ int pick_lanes(const Csr& A, int opt) {
   int L = 1;
   while (L < 64 && 2.0 * L < mean) L <<= 1;
   return L;
-}
-
-int compute_tiles(Csr& A, hipStream_t s) {
-  int32_t* d = nullptr;
-  SPX_TRY(dalloc_n(&d, 4));
-  hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, s, d, (int64_t)4);
-  const int64_t nb32 = ceil_div(A.n, 32);
-  if (nb32 > 0)
-    hipLaunchKernelGGL(k_tile_nnz, dim3((unsigned)ceil_div(nb32, 256)), dim3(256), 0, s, A.rowptr,
-                       A.n, d);
-  int32_t hostv[4] = {0, 0, 0, 0};
-  hipError_t e = hipMemcpyAsync(hostv, d, sizeof(hostv), hipMemcpyDeviceToHost, s);
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
-  dfree(d);
-  if (e != hipSuccess) return set_error(SPX_HIP_ERROR, "tile sizes: %s", hipGetErrorString(e));
-  for (int k = 0; k < 4; ++k) A.tile_nnz[k] = hostv[k];
-  return SPX_OK;
 }
 
 namespace {

@@ -2,10 +2,12 @@
 // tile of kWinRows rows, the ascending list of the kWinBlock-entry blocks of
 // x that its columns fall in, and each entry's position in that list.
 // Built on the device once per pattern (after the symbolic assembly, and for
-// the explicit transpose when it is built): one pass marks each tile's
-// blocks in an LDS bitmap and counts them, a scan turns the counts into
-// offsets, and a second pass writes the block lists and the 16-bit window
-// columns.  Values are never touched, so set_values_coo keeps it valid.
+// the explicit transpose when it is built): one kernel marks each tile's
+// blocks in an LDS bitmap, numbers them and writes the tile's list and its
+// 16-bit window columns; a scan of the lists' lengths and a small copy then
+// put the lists back to back.  The host reads only the statistics, and
+// drops the index where it would not pay.  Values are never touched, so
+// set_values_coo keeps it valid.
 #include <algorithm>
 #include <climits>
 
@@ -36,48 +38,34 @@ __device__ __forceinline__ int32_t wg_max(int32_t v, int32_t* red) {
   return max(max(red[0], red[1]), max(red[2], red[3]));
 }
 
-__device__ __forceinline__ int32_t wg_sum(int32_t v, int32_t* red) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-  __syncthreads();
-  return red[0] + red[1] + red[2] + red[3];
-}
-
-// Marks the blocks of entries [t0, t1) in bits (relative to block lo).
-__device__ __forceinline__ void mark_blocks(const int32_t* __restrict__ col, int32_t t0, int32_t t1,
-                                            int32_t lo, uint32_t* bits) {
-  bits[threadIdx.x] = 0;
-  __syncthreads();
-  for (int32_t e = t0 + (int32_t)threadIdx.x; e < t1; e += kWinRows) {
-    const int32_t d = col[e] / kWinBlock - lo;
-    atomicOr(&bits[d >> 5], 1u << (d & 31));
-  }
-  __syncthreads();
-}
-
-// Per tile: blocks in its window (0 if it gets none) and its lowest block.
-// stats[0] += entries of tiles without a window; stats[1] = largest window.
-__global__ __launch_bounds__(kWinRows) void k_win_count(int64_t n, const int32_t* __restrict__ rowptr,
+// Per tile: cnt[t] blocks in its window (0 if it gets none), their numbers
+// ascending in list[t kWinMaxBlocks ..], and lcol[e] = (rank of e's block) *
+// kWinBlock + col[e] % kWinBlock.  stats[0] += entries of tiles without a
+// window; stats[1] = largest window.  Does nothing once *off is set (the
+// pattern is then not the final one).  The tile's columns are read three
+// times, the later ones from the caches.
+__global__ __launch_bounds__(kWinRows) void k_win_tiles(int64_t n, const int32_t* __restrict__ rowptr,
                                                         const int32_t* __restrict__ col,
+                                                        const uint32_t* __restrict__ off,
                                                         uint32_t* __restrict__ cnt,
-                                                        int32_t* __restrict__ lo_out,
+                                                        int32_t* __restrict__ list,
+                                                        uint16_t* __restrict__ lcol,
                                                         unsigned long long* __restrict__ stats) {
   __shared__ uint32_t bits[kWinWords];
+  __shared__ uint32_t incl[kWinWords];
   __shared__ int32_t red[kWinRows / 64];
+  if (off && *off) return;
   const int64_t t = blockIdx.x;
   const int64_t r0 = t * kWinRows;
   const int64_t r1 = r0 + kWinRows < n ? r0 + kWinRows : n;
   const int32_t t0 = rowptr[r0], t1 = rowptr[r1];
+  const int tid = threadIdx.x;
   if (t0 == t1) {
-    if (threadIdx.x == 0) {
-      cnt[t] = 0;
-      lo_out[t] = 0;
-    }
+    if (tid == 0) cnt[t] = 0;
     return;
   }
   int32_t lo = INT_MAX, hi = -1;
-  for (int32_t e = t0 + (int32_t)threadIdx.x; e < t1; e += kWinRows) {
+  for (int32_t e = t0 + tid; e < t1; e += kWinRows) {
     const int32_t b = col[e] / kWinBlock;
     lo = min(lo, b);
     hi = max(hi, b);
@@ -85,145 +73,136 @@ __global__ __launch_bounds__(kWinRows) void k_win_count(int64_t n, const int32_t
   lo = wg_min(lo, red);
   hi = wg_max(hi, red);
   int32_t c = 0;
+  uint32_t word = 0;
   if (hi - lo < kWinSpan) {
-    mark_blocks(col, t0, t1, lo, bits);
-    c = wg_sum(__popc(bits[threadIdx.x]), red);
+    bits[tid] = 0;
+    __syncthreads();
+    // most entries find their block marked: a read shared by the wave
+    // instead of one atomic after the other on the same word
+    for (int32_t e = t0 + tid; e < t1; e += kWinRows) {
+      const int32_t d = col[e] / kWinBlock - lo;
+      const uint32_t m = 1u << (d & 31);
+      if (!(__hip_atomic_load(&bits[d >> 5], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) & m))
+        atomicOr(&bits[d >> 5], m);
+    }
+    __syncthreads();
+    // inclusive counts of the bitmap's words
+    word = bits[tid];
+    int32_t inc = __popc(word);
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int32_t v = __shfl_up(inc, o, 64);
+      if ((tid & 63) >= o) inc += v;
+    }
+    if ((tid & 63) == 63) red[tid >> 6] = inc;
+    __syncthreads();
+    for (int k = 0; k < kWinRows / 64; ++k) {
+      if (k < (tid >> 6)) inc += red[k];
+      c += red[k];
+    }
+    incl[tid] = (uint32_t)inc;
     if (c > kWinMaxBlocks) c = 0;
   }
-  if (threadIdx.x == 0) {
+  if (tid == 0) {
     cnt[t] = (uint32_t)c;
-    lo_out[t] = lo;
+    // one address for every tile: an atomic only where it changes something
     if (c == 0)
       atomicAdd(&stats[0], (unsigned long long)(t1 - t0));
-    else
+    else if ((unsigned long long)c >
+             __hip_atomic_load(&stats[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
       atomicMax(&stats[1], (unsigned long long)c);
   }
-}
-
-// Per tile with a window: blk[ptr[t] ..] = its blocks ascending, and
-// lcol[e] = (rank of e's block) * kWinBlock + col[e] % kWinBlock.
-__global__ __launch_bounds__(kWinRows) void k_win_emit(int64_t n, const int32_t* __restrict__ rowptr,
-                                                       const int32_t* __restrict__ col,
-                                                       const int32_t* __restrict__ ptr,
-                                                       const int32_t* __restrict__ lo_in,
-                                                       int32_t* __restrict__ blk,
-                                                       uint16_t* __restrict__ lcol) {
-  __shared__ uint32_t bits[kWinWords];
-  __shared__ uint32_t incl[kWinWords];
-  const int64_t t = blockIdx.x;
-  const int32_t k0 = ptr[t];
-  if (ptr[t + 1] == k0) return;
-  const int64_t r0 = t * kWinRows;
-  const int64_t r1 = r0 + kWinRows < n ? r0 + kWinRows : n;
-  const int32_t t0 = rowptr[r0], t1 = rowptr[r1];
-  const int32_t lo = lo_in[t];
-  const int tid = threadIdx.x;
-  mark_blocks(col, t0, t1, lo, bits);
-  const uint32_t w = bits[tid];
-  incl[tid] = __popc(w);
+  if (c == 0) return;
+  uint32_t rank = incl[tid] - __popc(word);
+  for (uint32_t m = word; m != 0; m &= m - 1)
+    list[t * kWinMaxBlocks + rank++] = lo + tid * 32 + (__ffs(m) - 1);
   __syncthreads();
-  for (int o = 1; o < kWinWords; o <<= 1) {
-    const uint32_t v = tid >= o ? incl[tid - o] : 0u;
-    __syncthreads();
-    incl[tid] += v;
-    __syncthreads();
-  }
-  uint32_t rank = incl[tid] - __popc(w);
-  for (uint32_t m = w; m != 0; m &= m - 1) blk[k0 + rank++] = lo + tid * 32 + (__ffs(m) - 1);
   for (int32_t e = t0 + tid; e < t1; e += kWinRows) {
-    const int32_t c = col[e];
-    const int32_t d = c / kWinBlock - lo;
-    const uint32_t word = bits[d >> 5];
-    const uint32_t r = incl[d >> 5] - __popc(word) + __popc(word & ((1u << (d & 31)) - 1u));
-    lcol[e] = (uint16_t)(r * kWinBlock + c % kWinBlock);
+    const int32_t cc = col[e];
+    const int32_t d = cc / kWinBlock - lo;
+    const uint32_t w = bits[d >> 5];
+    const uint32_t r = incl[d >> 5] - __popc(w) + __popc(w & ((1u << (d & 31)) - 1u));
+    lcol[e] = (uint16_t)(r * kWinBlock + cc % kWinBlock);
   }
 }
 
-__global__ void k_win_zero(unsigned long long* p) {
-  if (threadIdx.x < 2) p[threadIdx.x] = 0;
+// The lists back to back at ptr (a wave per tile), unless they exceed cap
+// (the index is then dropped).
+__global__ __launch_bounds__(kWinRows) void k_win_lists(int64_t tiles, const int32_t* __restrict__ ptr,
+                                                        const int32_t* __restrict__ list,
+                                                        int64_t cap, int32_t* __restrict__ blk) {
+  const int64_t t = (int64_t)blockIdx.x * (kWinRows / 64) + (threadIdx.x >> 6);
+  if (t >= tiles || ptr[tiles] > cap) return;
+  const int32_t k0 = ptr[t], c = ptr[t + 1] - k0;
+  const int i = threadIdx.x & 63;
+  static_assert(kWinMaxBlocks <= 64, "a lane per block");
+  if (i < c) blk[k0 + i] = list[t * kWinMaxBlocks + i];
 }
 
-void release(Window& w) {
-  dfree(w.lcol);
-  dfree(w.ptr);
-  dfree(w.blk);
-  w = Window();
-}
+// An index that pays holds at most two x entries per matrix entry.
+int64_t most_blocks(int64_t nnz) { return 2 * nnz / kWinBlock; }
 
 }  // namespace
 
-// Builds A.win, or leaves it empty when the window walk would not pay: the
-// staged windows would hold more than two x entries per matrix entry, or
-// more than one entry in eight would sit in tiles without a window.  Out of
-// device memory for the index also leaves it empty (the products then take
-// another walk); other failures are reported.
-int build_window(Csr& A, hipStream_t s) {
-  release(A.win);
-  if (A.n == 0 || A.nnz == 0) return SPX_OK;
-  const int64_t tiles = ceil_div(A.n, kWinRows);
-  uint32_t* cnt = nullptr;
-  int32_t* lo = nullptr;
-  int32_t* ptr = nullptr;
-  uint32_t* scratch = nullptr;
-  unsigned long long* stats = nullptr;
-  int st = SPX_OK;
-  do {
-    if ((st = dalloc_n(&cnt, (size_t)tiles)) != SPX_OK) break;
-    if ((st = dalloc_n(&lo, (size_t)tiles)) != SPX_OK) break;
-    if ((st = dalloc_n(&ptr, (size_t)tiles + 1)) != SPX_OK) break;
-    if ((st = dalloc_n(&scratch, (size_t)scan_scratch_elems(tiles))) != SPX_OK) break;
-    if ((st = dalloc_n(&stats, 2)) != SPX_OK) break;
-    hipLaunchKernelGGL(k_win_zero, dim3(1), dim3(64), 0, s, stats);
-    hipLaunchKernelGGL(k_win_count, dim3((unsigned)tiles), dim3(kWinRows), 0, s, A.n, A.rowptr,
-                       A.col, cnt, lo, stats);
-    if ((st = exclusive_scan_u32(cnt, reinterpret_cast<uint32_t*>(ptr), tiles,
-                                 reinterpret_cast<uint32_t*>(ptr) + tiles, scratch, s)) != SPX_OK)
-      break;
-    unsigned long long hs[2] = {0, 0};
-    int32_t total = 0;
-    hipError_t e = hipMemcpyAsync(hs, stats, sizeof(hs), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipMemcpyAsync(&total, ptr + tiles, 4, hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e != hipSuccess) {
-      st = set_error(SPX_HIP_ERROR, "window index: %s", hipGetErrorString(e));
-      break;
-    }
-    const bool pays = hs[1] > 0 && (int64_t)total * kWinBlock <= 2 * A.nnz &&
-                      (int64_t)hs[0] * 8 <= A.nnz;
-    if (!pays) break;
-    Window w;
-    w.ptr = ptr;
-    w.max_blocks = (int64_t)hs[1];
-    w.total_blocks = total;
-    w.gather_entries = (int64_t)hs[0];
-    if ((st = dalloc_n(&w.lcol, (size_t)A.nnz)) != SPX_OK ||
-        (st = dalloc_n(&w.blk, (size_t)std::max<int32_t>(total, 1))) != SPX_OK) {
-      ptr = nullptr;  // released with w
-      release(w);
-      break;
-    }
-    hipLaunchKernelGGL(k_win_emit, dim3((unsigned)tiles), dim3(kWinRows), 0, s, A.n, A.rowptr, A.col,
-                       ptr, lo, w.blk, w.lcol);
-    if ((e = hipGetLastError()) != hipSuccess || (e = hipStreamSynchronize(s)) != hipSuccess) {
-      ptr = nullptr;
-      release(w);
-      st = set_error(SPX_HIP_ERROR, "window index: %s", hipGetErrorString(e));
-      break;
-    }
-    A.win = w;
-    ptr = nullptr;  // owned by A.win
-  } while (false);
-  (void)hipStreamSynchronize(s);
-  dfree(cnt);
-  dfree(lo);
-  dfree(ptr);
-  dfree(scratch);
-  dfree(stats);
+int64_t window_scratch(int64_t n) {
+  const int64_t tiles = ceil_div(n, kWinRows);
+  return tiles + tiles * kWinMaxBlocks + scan_scratch_elems(tiles);
+}
+
+int window_enqueue(const Csr& A, int64_t most, const uint32_t* off, uint32_t* scratch,
+                   uint32_t* stats, hipStream_t s, Window* w) {
+  *w = Window();
+  if (A.n == 0 || most == 0) return SPX_OK;
+  const int64_t tiles = ceil_div(A.n, kWinRows), cap = most_blocks(most);
+  const int64_t words = tiles + 1 + cap;
+  int32_t* block = nullptr;
+  const int st = dalloc(reinterpret_cast<void**>(&block),
+                        (size_t)(words * 4 + most * (int64_t)sizeof(uint16_t) + 128));
   if (st == SPX_OUT_OF_MEMORY) {
     clear_error();
     return SPX_OK;
   }
-  return st;
+  SPX_TRY(st);
+  w->block = block;
+  w->ptr = block;
+  w->blk = block + tiles + 1;
+  w->lcol = reinterpret_cast<uint16_t*>(block + ((words + 15) & ~int64_t(15)));
+  uint32_t* cnt = scratch;
+  int32_t* list = reinterpret_cast<int32_t*>(scratch + tiles);
+  uint32_t* work = scratch + tiles + tiles * kWinMaxBlocks;
+  uint32_t* ptr = reinterpret_cast<uint32_t*>(w->ptr);
+  hipLaunchKernelGGL(k_win_tiles, dim3((unsigned)tiles), dim3(kWinRows), 0, s, A.n, A.rowptr, A.col,
+                     off, cnt, list, w->lcol, reinterpret_cast<unsigned long long*>(stats));
+  SPX_TRY(exclusive_scan_u32(cnt, ptr, tiles, ptr + tiles, work, s, 0, nullptr));
+  hipLaunchKernelGGL(k_win_lists, dim3((unsigned)ceil_div(tiles, kWinRows / 64)), dim3(kWinRows), 0,
+                     s, tiles, w->ptr, list, cap, w->blk);
+  SPX_CHECK_HIP(hipMemcpyAsync(stats + 4, ptr + tiles, sizeof(uint32_t), hipMemcpyDeviceToDevice, s));
+  SPX_CHECK_HIP(hipGetLastError());
+  return SPX_OK;
+}
+
+void window_release(Window* w) {
+  dfree(w->block);
+  *w = Window();
+}
+
+// Keeps w as A's index, or drops it when the window walk would not pay: the
+// staged windows would hold more than two x entries per matrix entry, or
+// more than one entry in eight would sit in tiles without a window.
+void window_keep(Csr& A, const uint32_t* stats, Window* w) {
+  window_release(&A.win);
+  const int64_t gather = (int64_t)(stats[0] | (uint64_t)stats[1] << 32);
+  const int64_t largest = (int64_t)(stats[2] | (uint64_t)stats[3] << 32);
+  const int64_t total = stats[4];
+  if (w->block && largest > 0 && total <= most_blocks(A.nnz) && gather * 8 <= A.nnz) {
+    A.win = *w;
+    A.win.max_blocks = largest;
+    A.win.total_blocks = total;
+    A.win.gather_entries = gather;
+    *w = Window();
+  } else {
+    window_release(w);
+  }
 }
 
 }  // namespace spx
