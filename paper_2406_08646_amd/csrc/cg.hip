@@ -171,6 +171,23 @@ __global__ __launch_bounds__(kBlock) void k_cg_spmv(int64_t n, const int32_t* __
   if (threadIdx.x == 0) P1[blockIdx.x] = dot;
 }
 
+// K1 by the pattern walk.
+template <typename VT, class P>
+__global__ __launch_bounds__(kBlock, P::per_cu) void k_cg_pattern(
+    int64_t n, const int32_t* __restrict__ rowptr, const VT* __restrict__ val,
+    const VT* __restrict__ p, VT* __restrict__ q, const CgScalars* __restrict__ st,
+    double* __restrict__ P1, WinView win) {
+  static_assert(kBlock == kWinRows, "one thread per row of a window tile");
+  extern __shared__ __align__(16) char smem[];
+  if (st->done) return;
+  double dot = 0.0;
+  pattern_product<P, true, VT>(n, rowptr, val, p, q, win, smem, [&](VT s, VT own, bool in) {
+    if (in) dot += (double)own * (double)s;
+  });
+  dot = block_sum<kBlock>(dot, reinterpret_cast<double*>(smem));
+  if (threadIdx.x == 0) P1[blockIdx.x] = dot;
+}
+
 // K2: alpha = rho_{k-1} / p.q; x += alpha p; r -= alpha q; partials of r.z, r.r
 template <typename VT>
 __global__ __launch_bounds__(kBlock) void k_cg_update(int64_t n, VT* __restrict__ x,
@@ -787,6 +804,7 @@ struct Op {
   const VT* val;
   SpmvShape sh;
   WinView win;
+  const Csr* m;  // its pattern
 };
 
 // Dynamic LDS of the solver kernels for elements of type VT (sh.lds is
@@ -805,6 +823,21 @@ size_t shape_lds(const SpmvShape& sh) {
   }
 }
 
+// K1 takes the pattern walk where the options leave the walk, its order and
+// its grid to the library, from two 256-row tiles per CU: below that the
+// resident solve takes what fits it and the stream walk's smaller tiles fill
+// the chip better.  Measured against the stream walk that these sizes had, ms
+// a solve: 27 points, 52^3 rows (2.1 tiles per CU) 5.0 and 4.6, 64^3 7.7 and
+// 6.2, 80^3 16.3 and 12.1; mixed precision, 64^3 8.2 and 5.7, 80^3 15.4 and
+// 9.8.
+constexpr int64_t kPatternTilesPerCu = 2;
+bool use_pattern(const spx_matrix* h, const SpmvShape& sh, const Csr& M) {
+  if (!M.win.patterned || !sh.nt || h->fused_opt > 0 || h->xcd_remap > 0) return false;
+  if (sh.variant == kVariantWindow) return true;
+  return h->variant_opt == kVariantAuto && !h->rows_opt && !h->rows32_opt && !h->vec_opt &&
+         !h->pipe_opt && !h->lanes_opt && ceil_div(M.n, kWinRows) >= kPatternTilesPerCu * cu_count();
+}
+
 // Enqueues iterations first .. first+count-1 (1-based k) of K1, K2, K3.
 // With `evs` (6 events per iteration) every kernel is bracketed by events.
 template <typename VT>
@@ -815,25 +848,47 @@ int enqueue_iterations(spx_matrix* h, const Work& w, const Op<VT>& A, VT* x, VT*
   const unsigned G2 = (unsigned)vector_blocks(h);
   double* P1 = w.partials;
   double* P2 = w.partials + G1;
-  const size_t lds = shape_lds<VT>(A.sh);
-  return with_shape<true>(A.sh, [&](auto shc) {
-    using SH = decltype(shc);
+  // K1 of iteration c, then K2 and K3 with its G partials
+  auto iterations = [&](unsigned G, auto&& k1) {
     for (int64_t c = 0; c < count; ++c) {
       const int64_t k = device_k ? 0 : first + c;
       hipEvent_t* e = evs ? evs + 6 * c : nullptr;
       if (e) (void)hipEventRecord(e[0], s);
-      hipLaunchKernelGGL((k_cg_spmv<SH, VT>), dim3(G1), dim3(kBlock), lds, s, A.n, A.rowptr, A.col,
-                         A.val, p, q, st, P1, A.sh.rows, remap_for(h, A.sh), A.sh.tile, A.win);
+      k1();
       if (e) (void)hipEventRecord(e[1], s);
       if (e) (void)hipEventRecord(e[2], s);
       hipLaunchKernelGGL((k_cg_update<VT>), dim3(G2), dim3(kBlock), 0, s, A.n, x, r, p, q, dinv, st,
-                         P1, (int64_t)G1, P2, k);
+                         P1, (int64_t)G, P2, k);
       if (e) (void)hipEventRecord(e[3], s);
       if (e) (void)hipEventRecord(e[4], s);
       hipLaunchKernelGGL((k_cg_pupdate<VT>), dim3(G2), dim3(kBlock), 0, s, A.n, p, r, dinv, st, P2,
                          (int64_t)G2, k);
       if (e) (void)hipEventRecord(e[5], s);
     }
+  };
+  if (use_pattern(h, A.sh, *A.m)) {
+    bool launched = false;
+    SPX_TRY(with_pattern<VT>(*A.m, [&](auto pat) -> int {
+      using P = decltype(pat);
+      const size_t lds = pattern_lds_bytes<P, VT>();
+      SPX_TRY(allow_lds(reinterpret_cast<const void*>(&k_cg_pattern<VT, P>), lds));
+      const unsigned G = pattern_blocks<P>(ceil_div(A.n, kWinRows), G1);
+      iterations(G, [&] {
+        hipLaunchKernelGGL((k_cg_pattern<VT, P>), dim3(G), dim3(kBlock), lds, s, A.n, A.rowptr, A.val,
+                           p, q, st, P1, A.win);
+      });
+      launched = true;
+      return SPX_OK;
+    }));
+    if (launched) return SPX_OK;
+  }
+  const size_t lds = shape_lds<VT>(A.sh);
+  return with_shape<true>(A.sh, [&](auto shc) {
+    using SH = decltype(shc);
+    iterations(G1, [&] {
+      hipLaunchKernelGGL((k_cg_spmv<SH, VT>), dim3(G1), dim3(kBlock), lds, s, A.n, A.rowptr, A.col,
+                         A.val, p, q, st, P1, A.sh.rows, remap_for(h, A.sh), A.sh.tile, A.win);
+    });
     return SPX_OK;
   });
 }
@@ -945,14 +1000,15 @@ template <typename VT>
 int chunk_graph(spx_matrix* h, const Work& w, const Op<VT>& A, VT* x, VT* r, VT* p, VT* q,
                 const VT* dinv, CgScalars* st, int32_t check_every, hipGraphExec_t* out) {
   spx_matrix::GraphCache& gc = h->graph[sizeof(VT) == 8 ? 0 : 1];
-  const uintptr_t key[16] = {(uintptr_t)A.rowptr, (uintptr_t)A.col, (uintptr_t)A.val,
+  const uintptr_t key[19] = {(uintptr_t)A.rowptr, (uintptr_t)A.col, (uintptr_t)A.val,
                              (uintptr_t)x, (uintptr_t)r, (uintptr_t)p, (uintptr_t)q,
                              (uintptr_t)dinv, (uintptr_t)st, (uintptr_t)w.partials,
                              (uintptr_t)check_every, (uintptr_t)fused_blocks(h),
                              (uintptr_t)vector_blocks(h),
                              (uintptr_t)(A.sh.variant * 4096 + A.sh.rows * 8 + A.sh.nt * 2 + A.sh.vec),
-                             (uintptr_t)(A.sh.tile * 64 + A.sh.lanes), (uintptr_t)(A.sh.pipe * 2 + remap_for(h, A.sh))};
-  if (gc.exec && std::equal(key, key + 16, gc.key)) {
+                             (uintptr_t)(A.sh.tile * 64 + A.sh.lanes), (uintptr_t)(A.sh.pipe * 2 + remap_for(h, A.sh)),
+                             (uintptr_t)A.n, (uintptr_t)A.win.row, (uintptr_t)use_pattern(h, A.sh, *A.m)};
+  if (gc.exec && std::equal(key, key + 19, gc.key)) {
     *out = gc.exec;
     return SPX_OK;
   }
@@ -978,7 +1034,7 @@ int chunk_graph(spx_matrix* h, const Work& w, const Op<VT>& A, VT* x, VT* r, VT*
   if (e_inst != hipSuccess)
     return set_error(SPX_HIP_ERROR, "cg graph instantiation failed: %s", hipGetErrorString(e_inst));
   gc.exec = exec;
-  std::copy(key, key + 16, gc.key);
+  std::copy(key, key + 19, gc.key);
   *out = exec;
   return SPX_OK;
 }
@@ -1168,7 +1224,7 @@ int cg_solve_impl(spx_matrix* h, const Work& w, const Csr& M, const double* b, d
     return set_error(SPX_INVALID_ARG, "cg_solve: bad maxit/check_every/rtol");
   if (maxit > INT32_MAX - 1) maxit = INT32_MAX - 1;
   const int64_t n = M.n;
-  const Op<double> A{n, M.rowptr, M.col, M.val, solver_shape(h, M), win_view(M)};
+  const Op<double> A{n, M.rowptr, M.col, M.val, solver_shape(h, M), win_view(M), &M};
   const int form = cg_form(h, M);
   double* r = w.vec;
   double* p = w.vec + n;
@@ -1399,8 +1455,8 @@ extern "C" int spx_cg_solve_mixed(spx_handle h, const double* b, double* x, doub
   const Csr& M = h->A;
   const int64_t n = M.n;
   const SpmvShape sh = solver_shape(h, M);
-  const Op<double> A64{n, M.rowptr, M.col, M.val, sh, win_view(M)};
-  const Op<float> A32{n, M.rowptr, M.col, M.val32, spmv_shape32(h, M), win_view(M)};
+  const Op<double> A64{n, M.rowptr, M.col, M.val, sh, win_view(M), &M};
+  const Op<float> A32{n, M.rowptr, M.col, M.val32, spmv_shape32(h, M), win_view(M), &M};
   float* r32 = h->work32;
   float* d32 = h->work32 + n;
   float* p32 = h->work32 + 2 * n;

@@ -96,6 +96,12 @@ constexpr int kWinRows = 256;
 constexpr int kWinBlock = 64;
 constexpr int kWinMaxBlocks = 64;
 constexpr int kWinSpan = 8192;
+// Row patterns of a window tile: most rows of a mesh operator have the same
+// window columns relative to their first one.  A tile of rows of up to
+// kPatLen entries with at most kPats different lists of such offsets has
+// them in pat, and each of its rows its first window column and its list.
+constexpr int kPats = 16;
+constexpr int kPatLen = 32;
 struct Window {
   void* block = nullptr;     // holds the three arrays
   uint16_t* lcol = nullptr;  // [nnz]
@@ -104,6 +110,9 @@ struct Window {
   int64_t max_blocks = 0;    // largest window of any tile
   int64_t total_blocks = 0;
   int64_t gather_entries = 0;  // entries of tiles without a window
+  uint32_t* row = nullptr;   // [n] first window column | number of the row's list << 16
+  uint16_t* pat = nullptr;   // [tiles][kPats][kPatLen] offsets, 0 past a list's end
+  bool patterned = false;    // row and pat hold every tile
 };
 
 // Rows of X a tile of `rows` consecutive rows of the matrix touches, for
@@ -124,6 +133,8 @@ struct WinView {
   const uint16_t* lcol;
   const int32_t* ptr;
   const int32_t* blk;
+  const uint32_t* row;
+  const uint16_t* pat;
 };
 
 struct Csr {
@@ -144,7 +155,9 @@ struct Csr {
   mutable bool grid_unfit = false, grid_unfit32 = false;
 };
 
-inline WinView win_view(const Csr& A) { return WinView{A.win.lcol, A.win.ptr, A.win.blk}; }
+inline WinView win_view(const Csr& A) {
+  return WinView{A.win.lcol, A.win.ptr, A.win.blk, A.win.row, A.win.pat};
+}
 
 // Resolved launch shape of a product on one matrix.
 struct SpmvShape {
@@ -234,7 +247,7 @@ struct spx_matrix {
   hipStream_t cap_stream = nullptr;
   struct GraphCache {
     hipGraphExec_t exec = nullptr;
-    uintptr_t key[16] = {};
+    uintptr_t key[19] = {};
   } graph[2];
 };
 

@@ -78,6 +78,15 @@ __global__ __launch_bounds__(kWinRows) void k_spmv_window(int64_t n, const int32
   if (threadIdx.x < r1 - r0) y[r0 + threadIdx.x] = s;
 }
 
+// The pattern walk (spmv_core.hpp).
+template <class P>
+__global__ __launch_bounds__(kWinRows, P::per_cu) void k_spmv_pattern(
+    int64_t n, const int32_t* __restrict__ rowptr, const double* __restrict__ val,
+    const double* __restrict__ x, double* __restrict__ y, WinView w) {
+  extern __shared__ __align__(16) char smem[];
+  pattern_product<P, false, double>(n, rowptr, val, x, y, w, smem, [](double, double, bool) {});
+}
+
 // One tile per workgroup, its columns and values staged by direct loads.
 template <int BLOCK>
 __global__ __launch_bounds__(BLOCK) void k_spmv_dma(int64_t n, const int32_t* __restrict__ rowptr,
@@ -614,6 +623,19 @@ int launch_spmv(const Csr& A, const SpmvShape& sh, const double* x, double* y, i
   if (A.n == 0) return SPX_OK;
   if (sh.variant == kVariantWindow) {
     const int64_t nb = ceil_div(A.n, kWinRows);
+    if (sh.nt && !remap) {  // the pattern walk has no other loads and order
+      bool launched = false;
+      SPX_TRY(with_pattern<double>(A, [&](auto p) -> int {
+        using P = decltype(p);
+        const size_t bytes = pattern_lds_bytes<P, double>();
+        SPX_TRY(allow_lds(reinterpret_cast<const void*>(&k_spmv_pattern<P>), bytes));
+        hipLaunchKernelGGL(k_spmv_pattern<P>, dim3(pattern_blocks<P>(nb)), dim3(kWinRows), bytes, s,
+                           A.n, A.rowptr, A.val, x, y, win_view(A));
+        launched = true;
+        return SPX_OK;
+      }));
+      if (launched) return SPX_OK;
+    }
     const size_t lds =
         window_lds_bytes(A.win.max_blocks, sizeof(double), kWinUProduct * win_v<double>());
     if (sh.nt)

@@ -572,4 +572,193 @@ __host__ __device__ inline size_t window_lds_bytes(int64_t max_blocks, size_t by
   return ((size_t)kWinRows * per_thread + (size_t)max_blocks * kWinBlock) * bytes;
 }
 
+// ------------------------------------------------------------ pattern walk
+// The window walk for patterns whose every tile has row patterns (Window):
+// an entry's window column is its row's first one plus its list's offset, so
+// the columns are not read at all: 8 bytes an entry instead of 10 in fp64, 4
+// instead of 6 in fp32, and 4 bytes and a 1 KB share of the lists a row.
+//
+// The product is bound by HBM, and what keeps it from the rate of a plain
+// read are the stores of the row sums among the loads (34 MB a product of
+// 600 take 20 us of 107) and loads not in flight.  So a workgroup walks many
+// tiles, with all of a tile's loads in flight at once while the last tile's
+// rows are added from LDS, and holds its row sums in registers to store
+// several tiles' at a time; no load stands under a condition, and the scalar
+// loads that a tile's addresses come from are a tile ahead.  A thread adds
+// one row in entry order, product and sum rounded apart: the bits of the
+// other walks.  Measured on the 27-point operator, 128^3 rows: 106 us a
+// product by the window walk, 99 by a walk like this one that reads the
+// 16-bit columns, 83 by this one; 96^3 rows 48, 48, 42.5; 64^3 15.5, 15.8,
+// 13.6; 9 points, 1401^2 rows 40.5 and 38.7; 5 points, 1800^2 rows 47 and
+// 43.  In the solvers' first kernel (128^3, fp64) 112 and 92, and (96^3,
+// fp32) 37.6 and 26.0.
+//
+// A form of the walk: STEPS 16-byte loads of values per thread take a tile,
+// windows have up to 4 PRE blocks, PER_CU workgroups per CU fit the LDS and
+// registers, and each holds the results of HOLD tiles.
+template <int STEPS, int PRE, int PER_CU, int HOLD>
+struct Pattern {
+  static constexpr int steps = STEPS, pre = PRE, per_cu = PER_CU, hold = HOLD;
+};
+
+// The products y = A x of tiles blockIdx.x, blockIdx.x + gridDim.x, ...;
+// each(sum, x of the row where OWN, row < n) is called for every row.  Loads
+// past a tile's entries take its first ones again, and members past a row's
+// end read the next row's values and offset 0 (a window has at least one
+// block); neither is used.  Leaves the workgroup synchronised.
+template <class P, bool OWN, typename VT, typename Each>
+__device__ __forceinline__ void pattern_product(int64_t n, const int32_t* __restrict__ rowptr,
+                                                const VT* __restrict__ val,
+                                                const VT* __restrict__ x, VT* __restrict__ y,
+                                                const WinView& w, char* lds, Each&& each) {
+#pragma clang fp contract(off)
+  constexpr int V = 16 / sizeof(VT), U = P::steps, PRE = P::pre, H = P::hold;
+  constexpr int32_t C = kWinRows * U * V;
+  constexpr int kW = kWinRows / 64;
+  constexpr int kB = 8;  // entries of a row in flight together
+  static_assert(kPats * kPatLen == 2 * kWinRows, "two offsets per thread");
+  static_assert(kPatLen % kB == 0, "reads past a row stay in its list");
+  typedef typename VecN<VT, V>::type VV;
+  VT* vals = reinterpret_cast<VT*>(lds);
+  VT* xs = vals + C;
+  uint32_t* pats = reinterpret_cast<uint32_t*>(xs + PRE * kW * kWinBlock);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t tiles = (n + kWinRows - 1) / kWinRows, step = gridDim.x, first = blockIdx.x;
+  if (first >= tiles) return;
+  VV a[U];
+  VT xr[PRE], own = VT(0);
+  int32_t bq[PRE];
+  int32_t ra, re, ta, t0, t1;
+  uint32_t info, pt;
+  auto blocks = [&](int64_t tile) {
+    const int32_t b0 = w.ptr[tile], b1 = w.ptr[tile + 1];
+#pragma unroll
+    for (int i = 0; i < PRE; ++i) bq[i] = w.blk[max(min(b0 + wv + kW * i, b1 - 1), 0)];
+    t0 = rowptr[tile * kWinRows];
+    t1 = rowptr[min((tile + 1) * kWinRows, n)];
+  };
+  auto issue = [&](int64_t tile) {
+    const int64_t r0 = tile * kWinRows;
+    ra = rowptr[min(r0 + tid, n)];
+    re = rowptr[min(r0 + tid + 1, n)];
+    info = w.row[min(r0 + tid, n - 1)];
+    pt = reinterpret_cast<const uint32_t*>(w.pat)[tile * kWinRows + tid];
+    if constexpr (OWN) own = x[min(r0 + tid, n - 1)];
+#pragma unroll
+    for (int i = 0; i < PRE; ++i) xr[i] = x[min((int64_t)bq[i] * kWinBlock + lane, n - 1)];
+    ta = t0 & ~(V - 1);
+    const int32_t cnt = t1 - ta;
+    const VT* va = val + ta;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int32_t e = (u * kWinRows + tid) * V;
+      a[u] = mload<true>(reinterpret_cast<const VV*>(va + (e < cnt ? e : 0)));
+    }
+  };
+  VT hold[H];
+  int held = 0;
+  int64_t row = first * kWinRows + tid;  // of hold[0]
+  auto flush = [&]() {
+#pragma unroll
+    for (int i = 0; i < H; ++i) {
+      const int64_t r = row + i * step * kWinRows;
+      if (i < held && r < n) y[r] = hold[i];
+    }
+    row += held * step * kWinRows;
+    held = 0;
+  };
+  blocks(first);
+  issue(first);
+  blocks(min(first + step, tiles - 1));
+  for (int64_t tile = first; tile < tiles; tile += step) {
+#pragma unroll
+    for (int i = 0; i < PRE; ++i) xs[(wv + kW * i) * kWinBlock + lane] = xr[i];
+    pats[tid] = pt;
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      *reinterpret_cast<VV*>(vals + (u * kWinRows + tid) * V) = a[u];
+    const VT* rv = vals + (ra - ta);
+    const int32_t len = re - ra;
+    const VT* rx = xs + (info & 0xffff);
+    const uint32_t* rp = pats + (info >> 16) * (kPatLen / 2);
+    const VT xo = own;
+    const int64_t next = tile + step;
+    if (next < tiles) {
+      issue(next);
+      blocks(min(next + step, tiles - 1));
+    }
+    __syncthreads();
+    VT s = VT(0);
+    for (int32_t k = 0; k < len; k += kB) {
+      uint32_t o[kB / 2];
+      VT v[kB], xv[kB];
+#pragma unroll
+      for (int j = 0; j < kB / 2; ++j) o[j] = rp[k / 2 + j];
+#pragma unroll
+      for (int j = 0; j < kB; ++j) v[j] = rv[k + j];
+#pragma unroll
+      for (int j = 0; j < kB; ++j) xv[j] = rx[j & 1 ? o[j / 2] >> 16 : o[j / 2] & 0xffff];
+#pragma unroll
+      for (int j = 0; j < kB; ++j) {
+        const VT m = v[j] * xv[j], t = s + m;
+        s = k + j < len ? t : s;
+      }
+    }
+    each(s, xo, row + held * step * kWinRows < n);
+#pragma unroll
+    for (int i = 0; i < H; ++i) hold[i] = i == held ? s : hold[i];
+    if (++held == H) flush();
+    __syncthreads();
+  }
+  flush();
+}
+
+template <class P, typename VT>
+constexpr size_t pattern_lds_bytes() {
+  return (size_t)(kWinRows * P::steps * (16 / sizeof(VT)) + P::pre * (kWinRows / 64) * kWinBlock) * sizeof(VT) +
+         kPats * kPatLen * sizeof(uint16_t);
+}
+
+// Workgroups of a launch over `tiles` tiles: every one of them takes the same
+// number of tiles, or one less.
+template <class P>
+unsigned pattern_blocks(int64_t tiles, int64_t limit = INT32_MAX) {
+  const int64_t most = std::min<int64_t>({tiles, limit, (int64_t)P::per_cu * cu_count()});
+  return (unsigned)ceil_div(tiles, ceil_div(tiles, most));
+}
+
+// Raises a kernel's LDS limit where it needs that.
+inline int allow_lds(const void* fn, size_t bytes) {
+  if (bytes > 64 * 1024)
+    SPX_CHECK_HIP(
+        hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
+  return SPX_OK;
+}
+
+// Calls f with the form of the pattern walk that holds A's largest tile and
+// window, if there is one: 5, 9 and 27 entries a row are 3, 5 and 14 steps in
+// fp64, 2, 3 and 7 in fp32, with windows of 16 to 24 blocks on meshes of up
+// to 2000 rows a line.  Measured workgroups per CU, us a product: 3 steps 86
+// with 4, 96 with 5 (spilling), 5 steps 78 with 4 and 79 with 5; 14 steps
+// need 70 KB of LDS and take 2; fp32, ms a solve: 7 steps 17.8 with 4, 17.4
+// with 3 and 17.3 with 5 on 96^3 rows, 37.8, 37.7 and 39.8 on 128^3; 3 steps
+// 383 with 6, 386 with 5, 493 with 8.
+template <typename VT, typename F>
+int with_pattern(const Csr& A, F&& f) {
+  if (!A.win.patterned) return SPX_OK;
+  constexpr int64_t V = 16 / sizeof(VT);
+  const int64_t steps = ceil_div(A.tile_nnz[3] + V - 1, kWinRows * V), blocks = A.win.max_blocks;
+  if constexpr (sizeof(VT) == 8) {
+    if (steps <= 3 && blocks <= 20) return f(Pattern<3, 5, 4, 4>());
+    if (steps <= 5 && blocks <= 20) return f(Pattern<5, 5, 4, 4>());
+    if (steps <= 14 && blocks <= 24) return f(Pattern<14, 6, 2, 16>());
+    if (steps <= 14 && blocks <= 32) return f(Pattern<14, 8, 2, 16>());
+  } else {
+    if (steps <= 3 && blocks <= 20) return f(Pattern<3, 5, 6, 8>());
+    if (steps <= 7 && blocks <= 24) return f(Pattern<7, 6, 4, 8>());
+    if (steps <= 7 && blocks <= 32) return f(Pattern<7, 8, 4, 8>());
+  }
+  return SPX_OK;
+}
 }  // namespace spx

@@ -18,6 +18,7 @@ namespace spx {
 
 namespace {
 
+constexpr int kPatTry = 4;
 constexpr int kWinWords = kWinSpan / 32;  // bitmap words of one tile
 static_assert(kWinWords == kWinRows, "one bitmap word per thread");
 static_assert(kWinMaxBlocks * kWinBlock <= 65536, "window columns fit in 16 bits");
@@ -44,16 +45,27 @@ __device__ __forceinline__ int32_t wg_max(int32_t v, int32_t* red) {
 // window; stats[1] = largest window.  Does nothing once *off is set (the
 // pattern is then not the final one).  The tile's columns are read three
 // times, the later ones from the caches.
+// Also the tile's row patterns (row and pat, see Window): the lists are
+// found one after the other, each the first row's that has none yet, and
+// compared with every such row's in LDS.  A mesh tile has 1 to about 12; a
+// tile whose first kPatTry lists hold less than a quarter of its rows is
+// given up.  *nopat is set where a tile has no patterns, and no further tile
+// looks for any.
 __global__ __launch_bounds__(kWinRows) void k_win_tiles(int64_t n, const int32_t* __restrict__ rowptr,
                                                         const int32_t* __restrict__ col,
                                                         const uint32_t* __restrict__ off,
                                                         uint32_t* __restrict__ cnt,
                                                         int32_t* __restrict__ list,
                                                         uint16_t* __restrict__ lcol,
-                                                        unsigned long long* __restrict__ stats) {
+                                                        unsigned long long* __restrict__ stats,
+                                                        uint32_t* __restrict__ row,
+                                                        uint16_t* __restrict__ pat,
+                                                        uint32_t* __restrict__ nopat) {
+  __shared__ uint16_t lc[kPatLen * kWinRows];
   __shared__ uint32_t bits[kWinWords];
   __shared__ uint32_t incl[kWinWords];
   __shared__ int32_t red[kWinRows / 64];
+  __shared__ int32_t range[2];
   if (off && *off) return;
   const int64_t t = blockIdx.x;
   const int64_t r0 = t * kWinRows;
@@ -62,6 +74,7 @@ __global__ __launch_bounds__(kWinRows) void k_win_tiles(int64_t n, const int32_t
   const int tid = threadIdx.x;
   if (t0 == t1) {
     if (tid == 0) cnt[t] = 0;
+    if (tid < r1 - r0) row[r0 + tid] = 0;
     return;
   }
   int32_t lo = INT_MAX, hi = -1;
@@ -112,7 +125,13 @@ __global__ __launch_bounds__(kWinRows) void k_win_tiles(int64_t n, const int32_t
              __hip_atomic_load(&stats[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
       atomicMax(&stats[1], (unsigned long long)c);
   }
-  if (c == 0) return;
+  if (c == 0) {
+    if (tid == 0) *nopat = 1;
+    return;
+  }
+  const int32_t rs = tid < r1 - r0 ? rowptr[r0 + tid] - t0 : 0;
+  const int32_t len = tid < r1 - r0 ? rowptr[r0 + tid + 1] - t0 - rs : 0;
+  const bool fit = __syncthreads_and(len <= kPatLen);
   uint32_t rank = incl[tid] - __popc(word);
   for (uint32_t m = word; m != 0; m &= m - 1)
     list[t * kWinMaxBlocks + rank++] = lo + tid * 32 + (__ffs(m) - 1);
@@ -122,8 +141,42 @@ __global__ __launch_bounds__(kWinRows) void k_win_tiles(int64_t n, const int32_t
     const int32_t d = cc / kWinBlock - lo;
     const uint32_t w = bits[d >> 5];
     const uint32_t r = incl[d >> 5] - __popc(w) + __popc(w & ((1u << (d & 31)) - 1u));
-    lcol[e] = (uint16_t)(r * kWinBlock + cc % kWinBlock);
+    const uint16_t v = (uint16_t)(r * kWinBlock + cc % kWinBlock);
+    lcol[e] = v;
+    if (fit) lc[e - t0] = v;
   }
+  __shared__ uint32_t quit;
+  if (tid == 0) quit = __hip_atomic_load(nopat, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();
+  if (quit) return;
+  int id = len > 0 ? -1 : 0;
+  bool found = fit;
+  for (int p = 0; found; ++p) {
+    const int32_t lead = wg_min(id < 0 ? tid : INT_MAX, red);
+    if (lead == INT_MAX) break;
+    if (tid == lead) {
+      range[0] = rs;
+      range[1] = len;
+    }
+    __syncthreads();
+    found = p < kPats;
+    if (!found) break;
+    const int32_t ls = range[0], ll = range[1];
+    if (id < 0 && len == ll) {
+      bool same = true;
+      for (int k = 1; same && k < len; ++k)
+        same = (uint16_t)(lc[rs + k] - lc[rs]) == (uint16_t)(lc[ls + k] - lc[ls]);
+      if (same) id = p;
+    }
+    if (tid < kPatLen)
+      pat[(t * kPats + p) * kPatLen + tid] = tid < ll ? (uint16_t)(lc[ls + tid] - lc[ls]) : 0;
+    if (p == kPatTry - 1) found = 4 * __syncthreads_count(id >= 0) >= kWinRows;
+  }
+  if (!found) {
+    if (tid == 0) *nopat = 1;
+    return;
+  }
+  if (tid < r1 - r0) row[r0 + tid] = (len > 0 ? lc[rs] : 0) | (uint32_t)id << 16;
 }
 
 // The lists back to back at ptr (a wave per tile), unless they exceed cap
@@ -154,10 +207,12 @@ int window_enqueue(const Csr& A, int64_t most, const uint32_t* off, uint32_t* sc
   *w = Window();
   if (A.n == 0 || most == 0) return SPX_OK;
   const int64_t tiles = ceil_div(A.n, kWinRows), cap = most_blocks(most);
-  const int64_t words = tiles + 1 + cap;
+  const int64_t words = tiles + 1 + cap, row = (words + 15) & ~int64_t(15);
+  const int64_t pat = (row + A.n + 15) & ~int64_t(15);
+  const int64_t lcol = pat + tiles * (kPats * kPatLen / 2);
   int32_t* block = nullptr;
   const int st = dalloc(reinterpret_cast<void**>(&block),
-                        (size_t)(words * 4 + most * (int64_t)sizeof(uint16_t) + 128));
+                        (size_t)(lcol * 4 + most * (int64_t)sizeof(uint16_t) + 128));
   if (st == SPX_OUT_OF_MEMORY) {
     clear_error();
     return SPX_OK;
@@ -166,13 +221,15 @@ int window_enqueue(const Csr& A, int64_t most, const uint32_t* off, uint32_t* sc
   w->block = block;
   w->ptr = block;
   w->blk = block + tiles + 1;
-  w->lcol = reinterpret_cast<uint16_t*>(block + ((words + 15) & ~int64_t(15)));
+  w->row = reinterpret_cast<uint32_t*>(block + row);
+  w->pat = reinterpret_cast<uint16_t*>(block + pat);
+  w->lcol = reinterpret_cast<uint16_t*>(block + lcol);
   uint32_t* cnt = scratch;
   int32_t* list = reinterpret_cast<int32_t*>(scratch + tiles);
   uint32_t* work = scratch + tiles + tiles * kWinMaxBlocks;
   uint32_t* ptr = reinterpret_cast<uint32_t*>(w->ptr);
   hipLaunchKernelGGL(k_win_tiles, dim3((unsigned)tiles), dim3(kWinRows), 0, s, A.n, A.rowptr, A.col,
-                     off, cnt, list, w->lcol, reinterpret_cast<unsigned long long*>(stats));
+                     off, cnt, list, w->lcol, reinterpret_cast<unsigned long long*>(stats), w->row, w->pat, stats + 5);
   SPX_TRY(exclusive_scan_u32(cnt, ptr, tiles, ptr + tiles, work, s, 0, nullptr));
   hipLaunchKernelGGL(k_win_lists, dim3((unsigned)ceil_div(tiles, kWinRows / 64)), dim3(kWinRows), 0,
                      s, tiles, w->ptr, list, cap, w->blk);
@@ -199,6 +256,7 @@ void window_keep(Csr& A, const uint32_t* stats, Window* w) {
     A.win.max_blocks = largest;
     A.win.total_blocks = total;
     A.win.gather_entries = gather;
+    A.win.patterned = stats[5] == 0;
     *w = Window();
   } else {
     window_release(w);
