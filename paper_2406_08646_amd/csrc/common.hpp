@@ -297,10 +297,20 @@ int launch_spmv(const Csr& A, const SpmvShape& sh, const double* x, double* y, i
                 hipStream_t s);
 int launch_spmm(const Csr& A, int64_t nrhs, const double* X, int64_t ldx, double* Y, int64_t ldy,
                 hipStream_t s);
+// Raises a kernel's LDS limit where it needs that.
+inline int allow_lds(const void* fn, size_t bytes) {
+  if (bytes > 64 * 1024)
+    SPX_CHECK_HIP(
+        hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
+  return SPX_OK;
+}
 // spmm.hip: the row-set index of A (once) and the 16-column product that
 // stages each tile's rows of X in LDS (X and Y contiguous, 16-byte aligned)
 int build_rowset(Csr& A, int rows, hipStream_t s);
 int launch_spmm_rowset(const Csr& A, const double* X, double* Y, hipStream_t s);
+// spmm.hip: the product by row patterns where it is the fastest
+int launch_spmm_pattern(const Csr& A, int64_t nrhs, const double* X, int64_t ldx, double* Y,
+                        int64_t ldy, hipStream_t s, bool* launched);
 // cg_grid.hip: a whole CG solve as one cooperative launch.  grid_cg_fits:
 // the pattern may take it.  launch_grid_cg: the fp64 solve with the work
 // vector u[n]; resets *st.  launch_grid_inner: the fp32 inner solve of the

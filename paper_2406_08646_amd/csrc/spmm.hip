@@ -517,6 +517,152 @@ __global__ __launch_bounds__(ROWS * kRpLanes) void k_spmm_rowset_pipe(
   }
 }
 
+// ------------------------------------------------------ pattern products
+// Y = A X where every tile of 256 rows has row patterns (Window), by the
+// panel of up to 2 Q columns: the panel's part of the tile's x window is
+// staged in LDS beside the tile's values, and Q neighbouring threads add a
+// row, two columns each, its columns in X given by its list of offsets.  The
+// values are loaded once a tile, whatever the number of panels.  As in the
+// product of one vector (spmv_core.hpp) a tile's loads are all in flight
+// while the last one's rows are added, none under a condition.  Entries are
+// added in order, as by the other kernels: the same bits.
+//
+// The kernels that gather X by entry are bound by the lines of the matrix
+// that a wave's rows, far apart, load again and again.  us a product, by
+// those and by this, with 2, 4, 6, 8, 12 and 24 columns: 27 points, 96^3 rows
+// 253 and 61, 288 and 72, 156 and 84, 154 and 104, 219 and 164, 402 and 295;
+// 9 points, 701^2 rows 26 and 16, 31 and 23, 39 and 33, 39 and 40, 56 and 64;
+// 5 points, 1001^2 rows 51 and 21, 58 and 34, 52 and 53, 52 and 64.  A window
+// of 16 blocks serves 256 short rows poorly once its columns fill the LDS
+// and one workgroup is left per CU.  Four entries of a row in flight take
+// the registers that allow this many waves (eight: 157 at 8 columns).
+//
+// A form: STEPS and PRE as in Pattern, Q threads per row, PER_CU workgroups.
+template <int STEPS, int PRE, int Q, int PER_CU>
+struct SpmmForm {
+  static constexpr int steps = STEPS, pre = PRE, q = Q, per_cu = PER_CU;
+  static constexpr int threads = kWinRows * Q;
+  static constexpr size_t lds = (size_t)kWinRows * STEPS * 16 + (size_t)PRE * 4 * kWinBlock * Q * 16 +
+                                kPats * kPatLen * sizeof(uint16_t);
+  static_assert(lds * PER_CU <= 160 * 1024, "the workgroups of a CU fit its LDS");
+};
+
+// A16: X and Y are 16-byte aligned with even strides.  A column past the last
+// is the last again, and is not stored.
+template <class F, bool A16>
+__global__ __launch_bounds__(F::threads, F::per_cu * F::q) void k_spmm_pattern(
+    int64_t n, const int32_t* __restrict__ rowptr, const double* __restrict__ val, int nrhs,
+    const double* __restrict__ X, int64_t ldx, double* __restrict__ Y, int64_t ldy, WinView w) {
+  constexpr int Q = F::q, PRE = F::pre, T = F::threads;
+  constexpr int kV = kWinRows * F::steps;   // 16-byte pieces of values
+  constexpr int U = (kV + T - 1) / T;
+  constexpr int kB = 4;  // entries of a row in flight together
+  extern __shared__ __align__(16) char smem[];
+  rs_d2* vals = reinterpret_cast<rs_d2*>(smem);
+  rs_d2* xs = vals + kV;
+  uint32_t* pats = reinterpret_cast<uint32_t*>(xs + PRE * 4 * kWinBlock * Q);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int q = tid % Q, lr = tid / Q;
+  const int slot = ((wv % Q) * 64 + lane) / Q;  // in its block of the window
+  const int xq = ((wv % Q) * 64 + lane) % Q;
+  const int64_t tiles = (n + kWinRows - 1) / kWinRows, step = gridDim.x;
+  const int panels = (nrhs + 2 * Q - 1) / (2 * Q);
+  rs_d2 a[U], xr[PRE];
+  int32_t bq[PRE];
+  int32_t ra, re, t0, t1;
+  uint32_t info, pt;
+  auto blocks = [&](int64_t tile) {
+    const int32_t b0 = w.ptr[tile], b1 = w.ptr[tile + 1];
+#pragma unroll
+    for (int i = 0; i < PRE; ++i) bq[i] = w.blk[max(min(b0 + wv / Q + 4 * i, b1 - 1), 0)];
+    t0 = rowptr[tile * kWinRows];
+    t1 = rowptr[min((tile + 1) * kWinRows, n)];
+  };
+  auto issue_x = [&](int c0) {
+    const int c = c0 + 2 * xq;
+    const int ca = min(c, nrhs - 1), cb = min(c + 1, nrhs - 1);
+#pragma unroll
+    for (int i = 0; i < PRE; ++i) {
+      const double* px = X + min((int64_t)bq[i] * kWinBlock + slot, n - 1) * ldx;
+      if constexpr (A16)
+        xr[i] = *reinterpret_cast<const rs_d2*>(px + min(c, (nrhs - 1) & ~1));
+      else
+        xr[i] = rs_d2{px[ca], px[cb]};
+    }
+  };
+  auto issue = [&](int64_t tile) {
+    const int64_t r = tile * kWinRows + lr;
+    ra = rowptr[min(r, n)];
+    re = rowptr[min(r + 1, n)];
+    info = w.row[min(r, n - 1)];
+    pt = reinterpret_cast<const uint32_t*>(w.pat)[tile * kWinRows + (tid & (kWinRows - 1))];
+    const int32_t ta = t0 & ~1, cnt = t1 - ta;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int32_t e = (u * T + tid) * 2;
+      a[u] = __builtin_nontemporal_load(reinterpret_cast<const rs_d2*>(val + ta + (e < cnt ? e : 0)));
+    }
+  };
+  int64_t tile = blockIdx.x;
+  if (tile >= tiles) return;
+  blocks(tile);
+  issue_x(0);
+  issue(tile);
+  for (; tile < tiles; tile += step) {
+    const int32_t len = re - ra;
+    const double* rv = reinterpret_cast<const double*>(vals) + (ra - (t0 & ~1));
+    const rs_d2* rx = xs + (info & 0xffff) * Q + q;
+    const uint32_t* rp = pats + (info >> 16) * (kPatLen / 2);
+    const int64_t row = tile * kWinRows + lr, next = tile + step;
+    if (tid < kWinRows) pats[tid] = pt;
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (u * T + tid < kV) vals[u * T + tid] = a[u];
+    for (int c0 = 0, panel = 0; panel < panels; ++panel, c0 += 2 * Q) {
+#pragma unroll
+      for (int i = 0; i < PRE; ++i) xs[((wv / Q + 4 * i) * kWinBlock + slot) * Q + xq] = xr[i];
+      if (panel + 1 < panels) {
+        issue_x(c0 + 2 * Q);
+      } else if (next < tiles) {
+        blocks(next);
+        issue_x(0);
+        issue(next);
+      }
+      __syncthreads();
+      rs_d2 s = {0.0, 0.0};
+      for (int32_t k = 0; k < len; k += kB) {
+        uint32_t o[kB / 2];
+        double v[kB];
+        rs_d2 x[kB];
+#pragma unroll
+        for (int j = 0; j < kB / 2; ++j) o[j] = rp[k / 2 + j];
+#pragma unroll
+        for (int j = 0; j < kB; ++j) v[j] = rv[k + j];
+#pragma unroll
+        for (int j = 0; j < kB; ++j) x[j] = rx[(j & 1 ? o[j / 2] >> 16 : o[j / 2] & 0xffff) * Q];
+#pragma unroll
+        for (int j = 0; j < kB; ++j) {
+          const double sx = fma(v[j], x[j].x, s.x), sy = fma(v[j], x[j].y, s.y);
+          s.x = k + j < len ? sx : s.x;
+          s.y = k + j < len ? sy : s.y;
+        }
+      }
+      const int c = c0 + 2 * q;
+      if (row < n && c < nrhs) {
+        double* py = Y + row * ldy + c;
+        if (A16 && c + 1 < nrhs) {
+          *reinterpret_cast<rs_d2*>(py) = s;
+        } else {
+          py[0] = s.x;
+          if (c + 1 < nrhs) py[1] = s.y;
+        }
+      }
+      __syncthreads();
+    }
+  }
+}
+
 template <int ROWS>
 int build_rowset_t(Csr& A, hipStream_t s) {
   RowSet& R = A.rs;
@@ -557,6 +703,62 @@ int build_rowset(Csr& A, int rows, hipStream_t s) {
   }
   R.rows = rows;
   R.built = true;
+  return SPX_OK;
+}
+
+// The pattern product where it is the fastest; *launched is false elsewhere.
+// By entries a row (steps) and the figures above: every width up to 32 but 16
+// on long rows (16 columns by row sets, below: 160 us, 204 by this), up to 6
+// on rows of about 9 entries and 4 on shorter ones; up to 8 there where X or
+// Y is not 16-byte aligned or has odd strides, as with odd numbers of columns
+// (the gathering kernels then load 8 bytes at a time: 5 columns on 501^2 rows
+// 20.5 and 16.9).  From one tile per CU (41^3 rows: 2 columns 21 and 11, 12
+// columns 24.5 and 21.8; below they are alike); more than 16 columns from
+// four (64^3: 24 columns 113 and 76; 41^3: 32 columns 39 and 47).
+int launch_spmm_pattern(const Csr& A, int64_t nrhs, const double* X, int64_t ldx, double* Y,
+                        int64_t ldy, hipStream_t s, bool* launched) {
+  *launched = false;
+  const int64_t tiles = ceil_div(A.n, kWinRows);
+  const int64_t steps = ceil_div(A.tile_nnz[3] + 1, kWinRows * 2), blocks = A.win.max_blocks;
+  const bool a16 = ((reinterpret_cast<uintptr_t>(X) | reinterpret_cast<uintptr_t>(Y)) & 15) == 0 &&
+                   ldx % 2 == 0 && ldy % 2 == 0;
+  const int64_t widest = steps > 5 ? 32 : !a16 ? 8 : steps > 3 ? 6 : 4;
+  if (!A.win.patterned || nrhs == 0 || nrhs == 16 || nrhs > widest ||
+      tiles < (nrhs > 16 ? 4 : 1) * (int64_t)cu_count())
+    return SPX_OK;
+  auto go = [&](auto f) -> int {
+    using F = decltype(f);
+    auto run = [&](auto k) -> int {
+      SPX_TRY(allow_lds(reinterpret_cast<const void*>(k), F::lds));
+      const int64_t most = std::min<int64_t>(tiles, (int64_t)F::per_cu * cu_count());
+      hipLaunchKernelGGL(k, dim3((unsigned)ceil_div(tiles, ceil_div(tiles, most))), dim3(F::threads),
+                         F::lds, s, A.n, A.rowptr, A.val, (int)nrhs, X, ldx, Y, ldy, win_view(A));
+      *launched = true;
+      return SPX_OK;
+    };
+    return a16 ? run(&k_spmm_pattern<F, true>) : run(&k_spmm_pattern<F, false>);
+  };
+  // threads per row: as few panels as fit the LDS, equally wide
+  const int64_t pairs = ceil_div(nrhs, 2), most_q = blocks <= 24 ? 4 : 3;
+  const int64_t q = ceil_div(pairs, ceil_div(pairs, most_q));
+  auto width = [&](auto q1, auto q2, auto q3, auto q4) -> int {
+    if (q <= 1) return go(q1);
+    if (q == 2) return go(q2);
+    if (q == 3) return go(q3);
+    return go(q4);
+  };
+  if (steps <= 3 && blocks <= 20)
+    return width(SpmmForm<3, 5, 1, 4>(), SpmmForm<3, 5, 2, 2>(), SpmmForm<3, 5, 3, 1>(),
+                 SpmmForm<3, 5, 4, 1>());
+  if (steps <= 5 && blocks <= 20)
+    return width(SpmmForm<5, 5, 1, 3>(), SpmmForm<5, 5, 2, 2>(), SpmmForm<5, 5, 3, 1>(),
+                 SpmmForm<5, 5, 4, 1>());
+  if (steps <= 14 && blocks <= 24)
+    return width(SpmmForm<14, 6, 1, 1>(), SpmmForm<14, 6, 2, 1>(), SpmmForm<14, 6, 3, 1>(),
+                 SpmmForm<14, 6, 4, 1>());
+  if (steps <= 14 && blocks <= 32)
+    return width(SpmmForm<14, 8, 1, 1>(), SpmmForm<14, 8, 2, 1>(), SpmmForm<14, 8, 3, 1>(),
+                 SpmmForm<14, 8, 3, 1>());
   return SPX_OK;
 }
 

@@ -750,7 +750,9 @@ extern "C" int spx_spmm(spx_handle h, int64_t nrhs, const double* X, int64_t ldx
     SPX_TRY(build_rowset(h->A, h->spmm_rows_opt ? h->spmm_rows_opt : 32, s));
     SPX_TRY(launch_spmm_rowset(h->A, X, Y, s));
   } else {
-    SPX_TRY(launch_spmm(h->A, nrhs, X, ldx, Y, ldy, s));
+    bool launched = false;
+    SPX_TRY(launch_spmm_pattern(h->A, nrhs, X, ldx, Y, ldy, s, &launched));
+    if (!launched) SPX_TRY(launch_spmm(h->A, nrhs, X, ldx, Y, ldy, s));
   }
   SPX_CHECK_HIP(hipGetLastError());
   return SPX_OK;

@@ -728,14 +728,6 @@ unsigned pattern_blocks(int64_t tiles, int64_t limit = INT32_MAX) {
   return (unsigned)ceil_div(tiles, ceil_div(tiles, most));
 }
 
-// Raises a kernel's LDS limit where it needs that.
-inline int allow_lds(const void* fn, size_t bytes) {
-  if (bytes > 64 * 1024)
-    SPX_CHECK_HIP(
-        hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
-  return SPX_OK;
-}
-
 // Calls f with the form of the pattern walk that holds A's largest tile and
 // window, if there is one: 5, 9 and 27 entries a row are 3, 5 and 14 steps in
 // fp64, 2, 3 and 7 in fp32, with windows of 16 to 24 blocks on meshes of up

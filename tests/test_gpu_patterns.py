@@ -2,12 +2,14 @@
 list lengths, window sizes and tile loads at the edges of its forms, patterns
 just past them, empty rows, ragged last tiles and values that must not
 spread, against the oracle."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
 
 from paper_2406_08646_amd import workloads as W
-from gpu_util import dev, host, require_gpu
+from gpu_util import dev, host, require_gpu, spmv_within
 
 pytestmark = pytest.mark.gpu
 
@@ -115,3 +117,62 @@ def test_pattern_solves(orc, shape, points):
         assert r.status == 0
         # the recursive residual's drift from the true one stays well below rtol
         assert np.linalg.norm(b - orc.spmv(ref, host(r.x))) <= 2e-10 * np.linalg.norm(b)
+
+
+# stencils on ragged meshes of more than one 256-row tile per CU (27n: four);
+# 27 points with windows of up to 24 blocks or, in 27w, more
+SPMM_SHAPES = {"5": ((311, 299), 5), "9": ((307, 303), 9), "27": ((47, 44, 43), 27),
+               "27w": ((51, 51, 51), 27), "27n": ((62, 64, 70), 27)}
+
+
+@pytest.mark.parametrize("name", sorted(SPMM_SHAPES))
+def test_pattern_spmm_bitwise(orc, name):
+    """Y = A X for every width that changes the form, contiguous, strided and
+    off a 16-byte boundary, has the bits of the gathering kernel (which takes
+    16 strided columns), and the oracle's values; nothing is written past a
+    row."""
+    spx = require_gpu()
+    shape, points = SPMM_SHAPES[name]
+    dim, n = len(shape), int(np.prod(shape))
+    idx = np.arange(n).reshape(shape)
+    I, J = [], []
+    for o in np.ndindex(*(3,) * dim):
+        o = [k - 1 for k in o]
+        if points == 5 and np.abs(o).sum() > 1:
+            continue
+        I.append(idx[tuple(slice(max(0, -k), s - max(0, k)) for k, s in zip(o, shape))].ravel())
+        J.append(idx[tuple(slice(max(0, k), s - max(0, -k)) for k, s in zip(o, shape))].ravel())
+    i, j = np.concatenate(I).astype(np.int32), np.concatenate(J).astype(np.int32)
+    rng = np.random.default_rng(31)
+    v = rng.uniform(-1, 1, i.size)
+    A = spx.coo_preallocate(n, dev(i), dev(j))
+    A.set_values_coo(dev(v))
+    ref = orc.assemble(n, i, j, v)
+    lib = spx.load_library()
+    stream = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    for nrhs, pad, shift in ((1, 0, 0), (2, 0, 0), (2, 0, 1), (3, 0, 0), (4, 2, 0), (5, 0, 0),
+                             (6, 0, 0), (7, 1, 0), (8, 0, 0), (11, 0, 0), (12, 0, 0), (15, 3, 1),
+                             (17, 0, 0), (24, 0, 0), (32, 0, 0), (33, 1, 0)):
+        print(name, n, nrhs, pad, shift, flush=True)
+        ld = nrhs + pad
+        Xh = rng.uniform(-1, 1, (n, nrhs))
+        X = torch.zeros(n * ld + 2, dtype=torch.float64, device="cuda")
+        Y = torch.full((n * ld + 2,), 7.0, dtype=torch.float64, device="cuda")
+        X[shift:shift + n * ld].view(n, ld)[:, :nrhs] = dev(Xh)
+        rc = lib.spx_spmm(A.handle, nrhs, ctypes.c_void_p(X.data_ptr() + 8 * shift), ld,
+                          ctypes.c_void_p(Y.data_ptr() + 8 * shift), ld, stream)
+        assert rc == 0
+        Yh = host(Y)
+        body = Yh[shift:shift + n * ld].reshape(n, ld)
+        assert np.all(body[:, nrhs:] == 7.0) and np.all(Yh[:shift] == 7.0)
+        assert np.all(Yh[shift + n * ld:] == 7.0)
+        for c in range(0, nrhs, 16):
+            Xg = torch.zeros(n, 18, dtype=torch.float64, device="cuda")
+            k = min(16, nrhs - c)
+            Xg[:, :k] = dev(np.ascontiguousarray(Xh[:, c:c + k]))
+            Yg = torch.zeros(n, 18, dtype=torch.float64, device="cuda")
+            assert lib.spx_spmm(A.handle, 16, ctypes.c_void_p(Xg.data_ptr()), 18,
+                                ctypes.c_void_p(Yg.data_ptr()), 18, stream) == 0
+            assert np.array_equal(bits(body[:, c:c + k]), bits(host(Yg)[:, :k]))
+    # the last product against the oracle
+    spmv_within(body[:, 0], orc.spmv(ref, Xh[:, 0]), orc.abs_spmv(ref, Xh[:, 0]))
