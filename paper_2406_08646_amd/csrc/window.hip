@@ -18,7 +18,7 @@ namespace spx {
 
 namespace {
 
-constexpr int kPatTry = 4;
+constexpr int kPatTry = 8;
 constexpr int kWinWords = kWinSpan / 32;  // bitmap words of one tile
 static_assert(kWinWords == kWinRows, "one bitmap word per thread");
 static_assert(kWinMaxBlocks * kWinBlock <= 65536, "window columns fit in 16 bits");
