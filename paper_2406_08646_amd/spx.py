@@ -151,16 +151,22 @@ def _check(rc: int, allowed=(OK,)) -> int:
     return rc
 
 
-def _stream(stream=None) -> ctypes.c_void_p:
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+# The smallest calls are bound by the host: a product on 4096 rows took 8.3 us
+# of it and 2 us of the GPU.  The helpers below therefore build no objects
+# (addresses are plain numbers, which c_void_p arguments accept, and the
+# current stream is asked for by number).
+def _stream(stream=None) -> int:
+    if stream is not None:
+        return stream.cuda_stream
+    if torch.cuda.is_initialized():
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _dev(t: torch.Tensor, dtype: torch.dtype, length: Optional[int], name: str) -> torch.Tensor:
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch tensor")
-    if t.device.type != "cuda":
+    if not t.is_cuda:
         raise ValueError(f"{name} must be a device (cuda) tensor")
     if t.dtype != dtype:
         raise TypeError(f"{name} must be {dtype}, got {t.dtype}")
@@ -171,8 +177,8 @@ def _dev(t: torch.Tensor, dtype: torch.dtype, length: Optional[int], name: str) 
     return t
 
 
-def _ptr(t: Optional[torch.Tensor]) -> ctypes.c_void_p:
-    return ctypes.c_void_p(0 if t is None or t.numel() == 0 else t.data_ptr())
+def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
+    return None if t is None or t.numel() == 0 else t.data_ptr()
 
 
 @dataclass
@@ -279,15 +285,19 @@ class Matrix:
     def matmult(self, x: torch.Tensor, y: Optional[torch.Tensor] = None, stream=None) -> torch.Tensor:
         _dev(x, torch.float64, self.n, "x")
         y = torch.empty_like(x) if y is None else _dev(y, torch.float64, self.n, "y")
-        _check(load_library().spx_matmult(self.handle, _ptr(x), _ptr(y), _stream(stream)))
+        rc = (_lib or load_library()).spx_matmult(self.handle, _ptr(x), _ptr(y), _stream(stream))
+        if rc:
+            _check(rc)
         return y
 
     def matmult_transpose(self, x: torch.Tensor, y: Optional[torch.Tensor] = None,
                           stream=None) -> torch.Tensor:
         _dev(x, torch.float64, self.n, "x")
         y = torch.empty_like(x) if y is None else _dev(y, torch.float64, self.n, "y")
-        _check(load_library().spx_matmult_transpose(self.handle, _ptr(x), _ptr(y),
-                                                    _stream(stream)))
+        rc = (_lib or load_library()).spx_matmult_transpose(self.handle, _ptr(x), _ptr(y),
+                                                            _stream(stream))
+        if rc:
+            _check(rc)
         return y
 
     def spmm(self, X: torch.Tensor, Y: Optional[torch.Tensor] = None, stream=None) -> torch.Tensor:
