@@ -277,7 +277,7 @@ int spx_batch_total_rows(spx_batch_handle b, int64_t* total);
  *   check_every: iterations between host polls, at which the workgroups are
  *     re-split among the systems still running (0 means 20).
  *   persistent: 1 asks for ONE launch for the whole solve, in which each
- *     workgroup (256 threads, 1024 when a system exceeds 1024 rows) takes
+ *     workgroup (256 threads, up to 1024 with larger systems) takes
  *     the next system from a queue, largest first, and runs the whole
  *     method on it alone (the fields above are then unused, and a system's
  *     largest 256-row tile, for BiCG also its transpose's, must fit 64 KB of
@@ -477,13 +477,15 @@ int spx_set_allocator(spx_alloc_fn alloc, spx_free_fn free, void* ctx);
  *     with columns and values moved into LDS by direct 16-byte loads, two
  *     staging buffers in the solver kernels), 4 window (tiles of 256 rows
  *     read the x entries they need from LDS, staged once per tile, and
- *     16-bit window columns instead of the 32-bit ones; results bitwise
+ *     16-bit window columns, or no columns where the rows of every tile
+ *     repeat a few patterns, instead of the 32-bit ones; results bitwise
  *     those of the stream walk; only for patterns with a window index, see
  *     spx_get_window, else as 0).  Auto takes the window walk when the
  *     pattern has an index and enough 256-row tiles per compute unit
  *     (smaller systems fill the chip better with the stream walk's smaller
  *     tiles): for MatMult and MatMultTranspose 2.5, for the solvers 12 (7
- *     when rows average at most 16 entries); and when rows average at most
+ *     when rows average at most 16 entries; 2 for the product of the CG
+ *     iteration where the rows repeat); and when rows average at most
  *     64 entries in every tile and
  *     none of SPX_OPT_ROWS_PER_BLOCK, SPX_OPT_QUAD_LOADS, SPX_OPT_PIPELINE
  *     is set.  Reading the option returns the variant MatMult resolves to.

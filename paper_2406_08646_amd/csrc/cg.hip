@@ -4,7 +4,8 @@
 // enqueues kernels and polls the flag every `check_every` iterations.
 //
 // One iteration k is three kernels, each fused around its memory traffic:
-//   K1  q = A p; per-workgroup partials of p.q
+//   K1  q = A p; per-workgroup partials of p.q (by row patterns where the
+//       matrix has them, the pattern walk, else by the matrix's own walk)
 //   K2  every workgroup adds the p.q partials (same fixed order, same
 //       result everywhere), alpha = rho_{k-1} / p.q; x += alpha p,
 //       r -= alpha q, z = D^-1 r; partials of r.z and r.r

@@ -5,7 +5,8 @@
 // walk over tiles of ROWS <= BLOCK rows, its products staged in `prod`
 // (LDS, at least as many doubles as the largest tile has entries); the dots
 // are workgroup sums.  No kernel is launched per iteration and no other
-// workgroup is waited for.
+// workgroup is waited for.  cg_solve_regs does the same, bit for bit, with
+// the rows' entries and vectors in registers, for systems that fit them.
 #pragma once
 
 #include <cmath>

@@ -15,6 +15,8 @@
 // Each row's products are added in entry order from +0.0, as the pair
 // kernels do, so the results are bitwise theirs, at every tile height
 // (16, 32 or 64 rows; SPX_OPT_SPMM_TILE_ROWS, 32 by default).
+//
+// The other widths where the matrix has row patterns: pattern products, below.
 #include <algorithm>
 
 #include <utility>
@@ -530,18 +532,23 @@ __global__ __launch_bounds__(ROWS * kRpLanes) void k_spmm_rowset_pipe(
 // The kernels that gather X by entry are bound by the lines of the matrix
 // that a wave's rows, far apart, load again and again.  us a product, by
 // those and by this, with 2, 4, 6, 8, 12 and 24 columns: 27 points, 96^3 rows
-// 253 and 61, 288 and 72, 156 and 84, 154 and 104, 219 and 164, 402 and 295;
-// 9 points, 701^2 rows 26 and 16, 31 and 23, 39 and 33, 39 and 40, 56 and 64;
-// 5 points, 1001^2 rows 51 and 21, 58 and 34, 52 and 53, 52 and 64.  A window
+// 253 and 61, 289 and 70, 157 and 81, 155 and 97, 219 and 157, 407 and 276;
+// 9 points, 701^2 rows 26 and 16, 31 and 22, 39 and 32, 39 and 40, 56 and 64;
+// 5 points, 1001^2 rows 51 and 21, 58 and 33, 52 and 46, 52 and 64.  A window
 // of 16 blocks serves 256 short rows poorly once its columns fill the LDS
-// and one workgroup is left per CU.  Four entries of a row in flight take
-// the registers that allow this many waves (eight: 157 at 8 columns).
+// and one workgroup is left per CU.  Two entries of a row in flight take the
+// registers that allow this many waves (8 columns: 97 us, 103 with four, 157
+// with eight).
 //
 // A form: STEPS and PRE as in Pattern, Q threads per row, PER_CU workgroups.
+// lean: more than 16 waves per CU, so 80 registers: a lane adds 32 bits to an
+// address of its wave's (5 points, 6 columns, 1001^2 rows 45 us where 64-bit
+// lane addresses spill and take 86; the other forms are 3 to 8% slower so).
 template <int STEPS, int PRE, int Q, int PER_CU>
 struct SpmmForm {
   static constexpr int steps = STEPS, pre = PRE, q = Q, per_cu = PER_CU;
   static constexpr int threads = kWinRows * Q;
+  static constexpr bool lean = PER_CU * Q > 4;
   static constexpr size_t lds = (size_t)kWinRows * STEPS * 16 + (size_t)PRE * 4 * kWinBlock * Q * 16 +
                                 kPats * kPatLen * sizeof(uint16_t);
   static_assert(lds * PER_CU <= 160 * 1024, "the workgroups of a CU fit its LDS");
@@ -556,7 +563,7 @@ __global__ __launch_bounds__(F::threads, F::per_cu * F::q) void k_spmm_pattern(
   constexpr int Q = F::q, PRE = F::pre, T = F::threads;
   constexpr int kV = kWinRows * F::steps;   // 16-byte pieces of values
   constexpr int U = (kV + T - 1) / T;
-  constexpr int kB = 4;  // entries of a row in flight together
+  constexpr int kB = 2;  // entries of a row in flight together
   extern __shared__ __align__(16) char smem[];
   rs_d2* vals = reinterpret_cast<rs_d2*>(smem);
   rs_d2* xs = vals + kV;
@@ -568,6 +575,7 @@ __global__ __launch_bounds__(F::threads, F::per_cu * F::q) void k_spmm_pattern(
   const int xq = ((wv % Q) * 64 + lane) % Q;
   const int64_t tiles = (n + kWinRows - 1) / kWinRows, step = gridDim.x;
   const int panels = (nrhs + 2 * Q - 1) / (2 * Q);
+  const uint32_t slotx = (uint32_t)slot * (uint32_t)ldx;
   rs_d2 a[U], xr[PRE];
   int32_t bq[PRE];
   int32_t ra, re, t0, t1;
@@ -584,7 +592,15 @@ __global__ __launch_bounds__(F::threads, F::per_cu * F::q) void k_spmm_pattern(
     const int ca = min(c, nrhs - 1), cb = min(c + 1, nrhs - 1);
 #pragma unroll
     for (int i = 0; i < PRE; ++i) {
-      const double* px = X + min((int64_t)bq[i] * kWinBlock + slot, n - 1) * ldx;
+      const double* px;
+      if constexpr (F::lean) {
+        const int64_t r0 = (int64_t)bq[i] * kWinBlock;
+        const uint32_t last = (uint32_t)min(n - 1 - r0, (int64_t)kWinBlock) * (uint32_t)ldx;
+        px = reinterpret_cast<const double*>(reinterpret_cast<const char*>(X + r0 * ldx) +
+                                             min(slotx, last) * 8u);
+      } else {
+        px = X + min((int64_t)bq[i] * kWinBlock + slot, n - 1) * ldx;
+      }
       if constexpr (A16)
         xr[i] = *reinterpret_cast<const rs_d2*>(px + min(c, (nrhs - 1) & ~1));
       else
@@ -708,13 +724,16 @@ int build_rowset(Csr& A, int rows, hipStream_t s) {
 
 // The pattern product where it is the fastest; *launched is false elsewhere.
 // By entries a row (steps) and the figures above: every width up to 32 but 16
-// on long rows (16 columns by row sets, below: 160 us, 204 by this), up to 6
-// on rows of about 9 entries and 4 on shorter ones; up to 8 there where X or
-// Y is not 16-byte aligned or has odd strides, as with odd numbers of columns
-// (the gathering kernels then load 8 bytes at a time: 5 columns on 501^2 rows
-// 20.5 and 16.9).  From one tile per CU (41^3 rows: 2 columns 21 and 11, 12
-// columns 24.5 and 21.8; below they are alike); more than 16 columns from
-// four (64^3: 24 columns 113 and 76; 41^3: 32 columns 39 and 47).
+// on long rows (16 columns by row sets, below: 160 us, 204 by this), up to 24
+// there where the windows leave panels of 6 columns (111^3 rows: 24 columns
+// 641 and 552, 32 columns 657 and 787); up to 6 on rows of about 9 entries;
+// on shorter ones up to 4, and 6 from ten tiles per CU (1001^2 rows 52 and
+// 46, 501^2 13.6 and 15.1); up to 8 on short rows where X or Y is not 16-byte
+// aligned or has odd strides, as with odd numbers of columns (the gathering
+// kernels then load 8 bytes at a time: 5 columns on 501^2 rows 20.5 and
+// 14.7).  From one tile per CU (41^3 rows: 2 columns 20 and 9.5, 12 columns
+// 24 and 21; below they are alike); more than 16 columns from four (64^3: 24
+// columns 113 and 70; 41^3: 32 columns 39 and 47).
 int launch_spmm_pattern(const Csr& A, int64_t nrhs, const double* X, int64_t ldx, double* Y,
                         int64_t ldy, hipStream_t s, bool* launched) {
   *launched = false;
@@ -722,8 +741,9 @@ int launch_spmm_pattern(const Csr& A, int64_t nrhs, const double* X, int64_t ldx
   const int64_t steps = ceil_div(A.tile_nnz[3] + 1, kWinRows * 2), blocks = A.win.max_blocks;
   const bool a16 = ((reinterpret_cast<uintptr_t>(X) | reinterpret_cast<uintptr_t>(Y)) & 15) == 0 &&
                    ldx % 2 == 0 && ldy % 2 == 0;
-  const int64_t widest = steps > 5 ? 32 : !a16 ? 8 : steps > 3 ? 6 : 4;
-  if (!A.win.patterned || nrhs == 0 || nrhs == 16 || nrhs > widest ||
+  const bool many = tiles >= 10 * (int64_t)cu_count();
+  const int64_t widest = steps > 5 ? (blocks <= 24 ? 32 : 24) : !a16 ? 8 : steps > 3 || many ? 6 : 4;
+  if (!A.win.patterned || nrhs == 0 || nrhs == 16 || nrhs > widest || ldx > (1 << 20) ||
       tiles < (nrhs > 16 ? 4 : 1) * (int64_t)cu_count())
     return SPX_OK;
   auto go = [&](auto f) -> int {
@@ -748,7 +768,7 @@ int launch_spmm_pattern(const Csr& A, int64_t nrhs, const double* X, int64_t ldx
     return go(q4);
   };
   if (steps <= 3 && blocks <= 20)
-    return width(SpmmForm<3, 5, 1, 4>(), SpmmForm<3, 5, 2, 2>(), SpmmForm<3, 5, 3, 1>(),
+    return width(SpmmForm<3, 5, 1, 4>(), SpmmForm<3, 5, 2, 2>(), SpmmForm<3, 5, 3, 2>(),
                  SpmmForm<3, 5, 4, 1>());
   if (steps <= 5 && blocks <= 20)
     return width(SpmmForm<5, 5, 1, 3>(), SpmmForm<5, 5, 2, 2>(), SpmmForm<5, 5, 3, 1>(),

@@ -1,6 +1,8 @@
 // Window index of a CSR pattern for the window walk of the products: per
 // tile of kWinRows rows, the ascending list of the kWinBlock-entry blocks of
 // x that its columns fall in, and each entry's position in that list.
+// Also, where every tile's rows repeat a few patterns, each row's pattern, so
+// that the products need not read the columns.
 // Built on the device once per pattern (after the symbolic assembly, and for
 // the explicit transpose when it is built): one kernel marks each tile's
 // blocks in an LDS bitmap, numbers them and writes the tile's list and its
