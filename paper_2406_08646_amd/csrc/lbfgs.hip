@@ -44,11 +44,10 @@ struct spx_lbfgs {
   int m = 0;
   int count = 0;  // pairs held
   int start = 0;  // slot of the oldest pair
-  int G = 0;      // workgroups of the pass kernels
   double* S = nullptr;   // [tiles][m][kTileRows]
   double* Y = nullptr;
   double* SY = nullptr;  // SY[a*m + b] = s_a . y_b, by slot
-  double* P = nullptr;   // partials [3 kMaxHistory][G]
+  double* P = nullptr;   // partials [3 kMaxHistory][workgroups of a pass]
   double* red = nullptr; // c[kMaxHistory] | e[kMaxHistory]
   double* a = nullptr;   // [tiles][kTileRows]
 };
@@ -60,7 +59,9 @@ constexpr int kMaxHistory = 64;
 constexpr int kLB = 256;
 constexpr int kWaves = kLB / 64;
 constexpr int kTileRows = 128;  // two rows per lane, 16-byte loads
-constexpr int kHold = 72;  // tiles of results held in LDS: half a CU's with the parts of k_lb_ya
+// Tiles of results held in LDS, by columns per wave: half a CU's LDS with the
+// parts of k_lb_ya, or less where eight workgroups share it.
+constexpr int hold_tiles(int nc) { return nc <= 2 ? 8 : 72; }
 constexpr int kWaveCols = kMaxHistory / kWaves;
 constexpr int kSolve = 1024;  // threads of the reduce-and-solve kernels
 constexpr int kRStride = kMaxHistory + 1;  // R in LDS, rows and columns both read by lane
@@ -200,7 +201,7 @@ __global__ __launch_bounds__(kLB) void k_lb_dots(int64_t n, int64_t tiles,
 // of P) in one pass over Y: each wave holds its quarter of the columns of a
 // tile in registers, the four waves' parts of Y c meet in LDS, and every
 // wave adds its columns' products with the tile's a.  a is held in LDS and
-// stored kHold tiles at a time (716 us against 749 stored tile by tile).
+// stored several tiles at a time (716 us against 749 stored tile by tile).
 template <int NC, bool H0>
 __global__ __launch_bounds__(kLB) void k_lb_ya(int64_t n, int64_t tiles,
                                                const double* __restrict__ Y, Ring R,
@@ -210,6 +211,7 @@ __global__ __launch_bounds__(kLB) void k_lb_ya(int64_t n, int64_t tiles,
                                                double* __restrict__ a_out,
                                                double* __restrict__ P) {
   __shared__ dbl2 part[2][kWaves][64];
+  constexpr int kHold = hold_tiles(NC);
   __shared__ dbl2 hold[kHold][64];
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const Cols<NC> C(R, w);
@@ -263,40 +265,40 @@ __global__ __launch_bounds__(kLB) void k_lb_ya(int64_t n, int64_t tiles,
 
 // ------------------------------------------------------------ p = a - S e
 // e in red[kMaxHistory ..): a wave per tile, kPU columns' loads in flight; p
-// is held in LDS and stored kHold / kWaves tiles at a time (658 us against
-// 702 stored tile by tile).  S e is summed before a, which mostly outweighs
-// it, is added.
+// is held in LDS and stored several tiles at a time (658 us against 702
+// stored tile by tile).  S e is summed before a, which mostly outweighs it, is
+// added.
 constexpr int kPU = 8;
+template <int NC>
 __global__ __launch_bounds__(kLB) void k_lb_p(int64_t n, int64_t tiles, const double* __restrict__ S,
                                               Ring R, const double* __restrict__ a,
                                               const double* __restrict__ red,
                                               double* __restrict__ p) {
+  constexpr int kHeld = hold_tiles(NC) / kWaves;
+  __shared__ dbl2 hold[kWaves][kHeld][64];
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const double* e = red + kMaxHistory;
   const bool wp = is_wide(p);
   const int cnt = R.cnt;
-  __shared__ dbl2 hold[kWaves][kHold / kWaves][64];
   const int64_t step = (int64_t)gridDim.x * kWaves;
   int64_t first = (int64_t)blockIdx.x * kWaves + w;
   int held = 0;
   for (int64_t t = first; t < tiles; t += step) {
-    const int64_t r = t * kTileRows + 2 * lane;
     const double* tile = S + t * R.m * kTileRows + 2 * lane;
-    const dbl2 av = *reinterpret_cast<const dbl2*>(a + r);
+    const dbl2 av = *reinterpret_cast<const dbl2*>(a + t * kTileRows + 2 * lane);
     dbl2 v = {0.0, 0.0};
-    int b = 0;
-    for (; b + kPU <= cnt; b += kPU) {
+    for (int b = 0; b < cnt; b += kPU) {
       dbl2 c[kPU];
 #pragma unroll
-      for (int u = 0; u < kPU; ++u)
-        c[u] = load_once(tile + R.slot(b + u) * kTileRows);
+      for (int u = 0; u < kPU; ++u) {
+        c[u] = dbl2{0.0, 0.0};
+        if (b + u < cnt) c[u] = load_once(tile + R.slot(b + u) * kTileRows);
+      }
 #pragma unroll
-      for (int u = 0; u < kPU; ++u) v += c[u] * e[b + u];
+      for (int u = 0; u < kPU; ++u) v += c[u] * (b + u < cnt ? e[b + u] : 0.0);
     }
-    for (; b < cnt; ++b)
-      v += load_once(tile + R.slot(b) * kTileRows) * e[b];
     hold[w][held][lane] = av - v;
-    if (++held == kHold / kWaves || t + step >= tiles) {
+    if (++held == kHeld || t + step >= tiles) {
       for (int i = 0; i < held; ++i) {
         const int64_t q = first + i * step;
         store2(p, q * kTileRows + 2 * lane, n, wp && (q + 1) * kTileRows <= n, hold[w][i][lane]);
@@ -451,12 +453,26 @@ __global__ void k_lb_scale(int64_t n, const double* __restrict__ g, const double
   if (i < n) p[i] = (h0 ? h0[i] : 1.0) * g[i];
 }
 
-// Calls f with the smallest of 4, 8, 12 and 16 columns per wave that hold a
+// Workgroups of the passes over cnt columns.  Two per CU: at m = 50 their
+// loads in flight (12 KB a wave) cover the memory's latency, and more make the
+// sums longer for nothing (the solves 11 and 17 us against 16 and 22 with
+// four; m = 16, n = 10^7, a step of 844 us against 888 with eight).  Up to 8
+// columns are too few bytes in flight for that, where the pass is long enough
+// for the sums not to matter: m = 3, n = 10^7 413 us with two per CU and 310
+// with eight (370 with whole columns), n = 10^6 54 and 46; n = 10^5 22 and 24.
+unsigned blocks(const spx_lbfgs* h, int cnt) {
+  const int64_t per_cu = cnt <= 2 * kWaves && h->tiles >= 4096 ? 8 : 2;
+  return (unsigned)std::min<int64_t>(h->tiles, per_cu * cu_count());
+}
+
+// Calls f with the smallest of 2, 4, 8, 12 and 16 columns per wave that hold a
 // quarter of cnt.
 template <typename F>
 void with_cols(int cnt, F&& f) {
   const int nc = (cnt + kWaves - 1) / kWaves;
-  if (nc <= 4)
+  if (nc <= 2)
+    f(std::integral_constant<int, 2>());
+  else if (nc <= 4)
     f(std::integral_constant<int, 4>());
   else if (nc <= 8)
     f(std::integral_constant<int, 8>());
@@ -478,7 +494,7 @@ namespace {
 int apply_passes(spx_lbfgs* h, const double* g, const double* h0, double* p, hipStream_t st,
                  bool have_q) {
   const int64_t n = h->n;
-  const unsigned G = (unsigned)h->G;
+  const unsigned G = blocks(h, h->count);
   const Ring R{h->m, h->start, h->count};
   if (have_q) {
     hipLaunchKernelGGL((k_lb_solve<true, 1>), dim3(1), dim3(kSolve), 0, st, h->P, (int64_t)G, R,
@@ -502,7 +518,10 @@ int apply_passes(spx_lbfgs* h, const double* g, const double* h0, double* p, hip
   });
   hipLaunchKernelGGL((k_lb_solve<false, 2>), dim3(1), dim3(kSolve), 0, st, h->P, (int64_t)G, R, 0,
                      h->SY, h->red);
-  hipLaunchKernelGGL(k_lb_p, dim3(G), dim3(kLB), 0, st, n, h->tiles, h->S, R, h->a, h->red, p);
+  with_cols(R.cnt, [&](auto nc) {
+    hipLaunchKernelGGL(k_lb_p<decltype(nc)::value>, dim3(G), dim3(kLB), 0, st, n, h->tiles, h->S, R,
+                       h->a, h->red, p);
+  });
   return SPX_OK;
 }
 }  // namespace
@@ -520,17 +539,13 @@ extern "C" int spx_lbfgs_create(int64_t n, int32_t m, void* stream, spx_lbfgs_ha
   h->n = n;
   h->m = m;
   h->tiles = ceil_div(n, kTileRows);
-  // two workgroups per CU: at m = 50 their loads in flight (51 KB each) cover
-  // the memory's latency, and three or four make the sums longer for nothing
-  // (the solves 11 and 17 us against 16 and 22)
-  h->G = (int)std::min<int64_t>((int64_t)cu_count() * 2, h->tiles);
   const size_t rows = (size_t)h->tiles * kTileRows;
   int st = SPX_OK;
   do {
     if ((st = dalloc_n(&h->S, rows * m)) != SPX_OK) break;
     if ((st = dalloc_n(&h->Y, rows * m)) != SPX_OK) break;
     if ((st = dalloc_n(&h->SY, (size_t)m * m)) != SPX_OK) break;
-    if ((st = dalloc_n(&h->P, (size_t)3 * kMaxHistory * h->G)) != SPX_OK) break;
+    if ((st = dalloc_n(&h->P, (size_t)3 * kMaxHistory * blocks(h, 1))) != SPX_OK) break;
     if ((st = dalloc_n(&h->red, (size_t)2 * kMaxHistory)) != SPX_OK) break;
     if ((st = dalloc_n(&h->a, rows)) != SPX_OK) break;
   } while (false);
@@ -587,7 +602,7 @@ int update_impl(spx_lbfgs* h, const double* s, const double* y, const double* g,
     start = (h->start + 1) % h->m;
     cnt = h->m;
   }
-  const unsigned G = (unsigned)h->G;
+  const unsigned G = blocks(h, cnt);
   const Ring R{h->m, start, cnt};
   hipLaunchKernelGGL(k_lb_put, dim3((unsigned)ceil_div(h->tiles, kWaves)), dim3(kLB), 0, st, h->n,
                      h->tiles, h->m, slot, s, y, h->S, h->Y);

@@ -1,5 +1,6 @@
 """GPU limited-memory BFGS product at the edges of its tiling: 128-row tiles,
-a quarter of the pairs per wave, results held over 72 tiles a workgroup."""
+a quarter of the pairs per wave, results held over 72 tiles a workgroup, or 8
+where long passes over few pairs take more workgroups."""
 import numpy as np
 import pytest
 import torch
@@ -19,7 +20,9 @@ def tol(n):
     (1, 1, 2), (2, 3, 2), (127, 4, 4), (128, 5, 7), (129, 16, 17), (1000, 17, 17),
     (513 * 128 + 1, 13, 14),     # more tiles than workgroups, a ragged last one
     (4096, 49, 64), (4097, 64, 64),
-    (512 * 72 * 128 + 129, 2, 3)])  # a workgroup's held results written twice
+    (512 * 72 * 128 + 129, 9, 10),  # a workgroup's held results written twice
+    (4095 * 128, 8, 8), (4096 * 128 - 1, 8, 9),  # either side of the eight-workgroup form
+    (2048 * 8 * 128 + 130, 3, 4)])  # and its held results written twice
 @pytest.mark.parametrize("offset", [0, 1])
 def test_lbfgs_tiles(orc, n, m, pushes, offset):
     """p against the oracle after the pushes, with every vector on or 8 bytes
