@@ -176,3 +176,37 @@ def test_pattern_spmm_bitwise(orc, name):
             assert np.array_equal(bits(body[:, c:c + k]), bits(host(Yg)[:, :k]))
     # the last product against the oracle
     spmv_within(body[:, 0], orc.spmv(ref, Xh[:, 0]), orc.abs_spmv(ref, Xh[:, 0]))
+
+
+def test_pattern_products_under_capture():
+    """A captured product and product of several vectors, both of the forms
+    that raise their LDS limit, replay with the eager bits on new inputs."""
+    spx = require_gpu()
+    idx = np.arange(62 * 64 * 70).reshape(62, 64, 70)
+    I, J = [], []
+    for o in np.ndindex(3, 3, 3):
+        o = [k - 1 for k in o]
+        I.append(idx[tuple(slice(max(0, -k), s - max(0, k)) for k, s in zip(o, idx.shape))].ravel())
+        J.append(idx[tuple(slice(max(0, k), s - max(0, -k)) for k, s in zip(o, idx.shape))].ravel())
+    i, j = np.concatenate(I).astype(np.int32), np.concatenate(J).astype(np.int32)
+    n = idx.size
+    A = spx.coo_preallocate(n, dev(i), dev(j))
+    A.set_values_coo(dev(np.random.default_rng(41).uniform(-1, 1, i.size)))
+    x, X = (torch.zeros(n, k, dtype=torch.float64, device="cuda").squeeze(1) for k in (1, 4))
+    y, Y = torch.empty_like(x), torch.empty_like(X)
+    A.matmult(x, y)
+    A.spmm(X, Y)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        A.matmult(x, y)
+        A.spmm(X, Y)
+    for seed in range(3):
+        x.copy_(dev(np.random.default_rng(seed).uniform(-1, 1, n)))
+        X.copy_(dev(np.random.default_rng(seed + 9).uniform(-1, 1, (n, 4))))
+        y.fill_(7.0)
+        Y.fill_(7.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(bits(host(y)), bits(host(A.matmult(x))))
+        assert np.array_equal(bits(host(Y)), bits(host(A.spmm(X))))
