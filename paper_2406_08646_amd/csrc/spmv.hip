@@ -743,8 +743,13 @@ extern "C" int spx_spmm(spx_handle h, int64_t nrhs, const double* X, int64_t ldx
     return set_error(SPX_INVALID_ARG, "spmm: bad argument");
   hipStream_t s = static_cast<hipStream_t>(stream);
   // 16 contiguous, 16-byte aligned columns: each tile's rows of X staged in
-  // LDS (spmm.hip), the index built on the first call
+  // LDS (spmm.hip), the index built on the first call; unless rows are so
+  // short that the staging does not pay (us, by row sets and gathered: 5
+  // points, 1001^2 rows 118 and 79, 501^2 30 and 21; 9 points, 701^2 rows 56
+  // and 58, 27 points, 96^3 rows 148 and over 200) and no tile height was
+  // asked for
   const bool rowset = nrhs == 16 && ldx == 16 && ldy == 16 &&
+                      (h->spmm_rows_opt || h->A.nnz > 7 * h->A.n) &&
                       ((reinterpret_cast<uintptr_t>(X) | reinterpret_cast<uintptr_t>(Y)) & 15) == 0;
   if (rowset) {
     SPX_TRY(build_rowset(h->A, h->spmm_rows_opt ? h->spmm_rows_opt : 32, s));

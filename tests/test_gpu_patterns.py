@@ -152,6 +152,7 @@ def test_pattern_spmm_bitwise(orc, name):
     stream = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
     for nrhs, pad, shift in ((1, 0, 0), (2, 0, 0), (2, 0, 1), (3, 0, 0), (4, 2, 0), (5, 0, 0),
                              (6, 0, 0), (7, 1, 0), (8, 0, 0), (11, 0, 0), (12, 0, 0), (15, 3, 1),
+                             (16, 0, 0), (16, 1, 0),
                              (17, 0, 0), (24, 0, 0), (32, 0, 0), (33, 1, 0)):
         print(name, n, nrhs, pad, shift, flush=True)
         ld = nrhs + pad
