@@ -270,7 +270,7 @@ int ensure_val32(spx_matrix* h, hipStream_t s);
 int pick_lanes(const Csr& A, int opt);
 // window.hip: the window index of a pattern of at most `most` entries.
 // window_enqueue allocates *w (empty when there is no memory for it) and
-// enqueues its kernels, which do nothing once *off is set; scratch:
+// enqueues its kernels, which write no index once *off is set; scratch:
 // window_scratch(n) words; stats: kWinStats words, zero, 8-byte aligned.
 // window_keep, with stats read back, moves *w to A or releases it.
 constexpr int kWinStats = 6;

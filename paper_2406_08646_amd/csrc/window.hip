@@ -44,9 +44,10 @@ __device__ __forceinline__ int32_t wg_max(int32_t v, int32_t* red) {
 // Per tile: cnt[t] blocks in its window (0 if it gets none), their numbers
 // ascending in list[t kWinMaxBlocks ..], and lcol[e] = (rank of e's block) *
 // kWinBlock + col[e] % kWinBlock.  stats[0] += entries of tiles without a
-// window; stats[1] = largest window.  Does nothing once *off is set (the
-// pattern is then not the final one).  The tile's columns are read three
-// times, the later ones from the caches.
+// window; stats[1] = largest window.  Once *off is set (the pattern is then
+// not the final one) every cnt is 0, so that their scan names no place, and
+// nothing else is written.  The tile's columns are read three times, the
+// later ones from the caches.
 // Also the tile's row patterns (row and pat, see Window): the lists are
 // found one after the other, each the first row's that has none yet, and
 // compared with every such row's in LDS.  A mesh tile has 1 to about 12; a
@@ -68,8 +69,11 @@ __global__ __launch_bounds__(kWinRows) void k_win_tiles(int64_t n, const int32_t
   __shared__ uint32_t incl[kWinWords];
   __shared__ int32_t red[kWinRows / 64];
   __shared__ int32_t range[2];
-  if (off && *off) return;
   const int64_t t = blockIdx.x;
+  if (off && *off) {
+    if (threadIdx.x == 0) cnt[t] = 0;
+    return;
+  }
   const int64_t r0 = t * kWinRows;
   const int64_t r1 = r0 + kWinRows < n ? r0 + kWinRows : n;
   const int32_t t0 = rowptr[r0], t1 = rowptr[r1];
@@ -181,13 +185,14 @@ __global__ __launch_bounds__(kWinRows) void k_win_tiles(int64_t n, const int32_t
   if (tid < r1 - r0) row[r0 + tid] = (len > 0 ? lc[rs] : 0) | (uint32_t)id << 16;
 }
 
-// The lists back to back at ptr (a wave per tile), unless they exceed cap
-// (the index is then dropped).
+// The lists back to back at ptr (a wave per tile), unless *off is set or they
+// exceed cap (the index is then dropped).
 __global__ __launch_bounds__(kWinRows) void k_win_lists(int64_t tiles, const int32_t* __restrict__ ptr,
                                                         const int32_t* __restrict__ list,
+                                                        const uint32_t* __restrict__ off,
                                                         int64_t cap, int32_t* __restrict__ blk) {
   const int64_t t = (int64_t)blockIdx.x * (kWinRows / 64) + (threadIdx.x >> 6);
-  if (t >= tiles || ptr[tiles] > cap) return;
+  if (t >= tiles || (off && *off) || (int64_t)(uint32_t)ptr[tiles] > cap) return;
   const int32_t k0 = ptr[t], c = ptr[t + 1] - k0;
   const int i = threadIdx.x & 63;
   static_assert(kWinMaxBlocks <= 64, "a lane per block");
@@ -234,7 +239,7 @@ int window_enqueue(const Csr& A, int64_t most, const uint32_t* off, uint32_t* sc
                      off, cnt, list, w->lcol, reinterpret_cast<unsigned long long*>(stats), w->row, w->pat, stats + 5);
   SPX_TRY(exclusive_scan_u32(cnt, ptr, tiles, ptr + tiles, work, s, 0, nullptr));
   hipLaunchKernelGGL(k_win_lists, dim3((unsigned)ceil_div(tiles, kWinRows / 64)), dim3(kWinRows), 0,
-                     s, tiles, w->ptr, list, cap, w->blk);
+                     s, tiles, w->ptr, list, off, cap, w->blk);
   SPX_CHECK_HIP(hipMemcpyAsync(stats + 4, ptr + tiles, sizeof(uint32_t), hipMemcpyDeviceToDevice, s));
   SPX_CHECK_HIP(hipGetLastError());
   return SPX_OK;
