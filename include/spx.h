@@ -507,9 +507,9 @@ int spx_set_allocator(spx_alloc_fn alloc, spx_free_fn free, void* ctx);
  *     spx_cg_solve and spx_cg_solve_transpose.  -1 (default): form 1 for
  *     matrices of at most 2,000,000 entries (where its saved launch and
  *     reduction point per iteration pay) unless SPX_OPT_GRAPH is on, form 0
- *     otherwise (the cooperative solve of SPX_OPT_SMALL_SOLVE is form 1 at
- *     any size); systems small enough for the one-workgroup solve still
- *     take it; reading the option returns the form a solve with A takes.
+ *     otherwise; systems that SPX_OPT_SMALL_SOLVE takes for its size take the
+ *     textbook form; reading the option returns the form that a larger
+ *     solve with A takes, by launches or as one cooperative launch.
  *     0: the textbook (Hestenes-Stiefel) form, three kernels and two
  *     reduction points per iteration.  1: the Chronopoulos-Gear single-reduction form of the same
  *     method (Sec. 6 names fewer synchronisation points as the aim of the
@@ -541,14 +541,16 @@ int spx_set_allocator(spx_alloc_fn alloc, spx_free_fn free, void* ctx);
  *     option, profiling, graph replay or the single-reduction form is set.
  *     2: whenever a 256-row tile fits in 64 KB of LDS.  Same recurrences,
  *     tests and statuses; the dots are summed in another order.  With 1,
- *     under the same conditions, and SPX_OPT_CG_VARIANT -1 or 1, a system
- *     of more than 256 rows whose matrix fits in the LDS of all compute
- *     units (about 10 bytes per entry, up to 524,288 rows) is solved in the
- *     single-reduction form by ONE
- *     cooperative launch, as are the fp32 inner solves of
- *     spx_cg_solve_mixed (about 6 bytes per entry); 0 keeps both to
- *     launches per iteration.  A pattern whose rows need too much of x per
- *     workgroup takes those as well.
+ *     rows of at most 9 entries (27 up to 256 rows) are held in the
+ *     workgroup's registers; and with no launch-shape option, profiling or
+ *     graph replay set, and SPX_OPT_CG_VARIANT -1 or 1, any other system of
+ *     more than 256 rows whose matrix fits in the LDS of all compute units
+ *     (about 10 bytes per entry, up to 524,288 rows) is solved by ONE
+ *     cooperative launch, in the form it would have had without: textbook
+ *     up to 2048 rows with SPX_OPT_CG_VARIANT -1, else that option's.  So
+ *     are the fp32 inner solves of spx_cg_solve_mixed (about 6 bytes per
+ *     entry); 0 keeps both to launches per iteration.  A pattern whose rows
+ *     need too much of x per workgroup takes those as well.
  *   SPX_OPT_IR_EARLY_EXIT: inner stopping rule of spx_cg_solve_mixed.
  *     0 (default): each inner solve runs to rtol_inner relative to its
  *     right-hand side.  1: it also stops once its residual is at most

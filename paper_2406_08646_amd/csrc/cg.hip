@@ -1152,9 +1152,10 @@ int finish_solve(spx_matrix* h, const Work& w, const Op<double>& A, const double
                  double* relres_out);
 
 // The one-workgroup solve: forced by SPX_OPT_SMALL_SOLVE = 2, chosen by the
-// default 1 for systems of at most kOneAutoRows rows that the resident solve
-// below leaves when no launch-shape option, profiling, graph replay or the single-reduction form asks for the
-// multi-workgroup kernels; either way only if a 256-row tile fits in 64 KB.
+// default 1 for systems of at most kOneAutoRows rows that neither use_regs nor
+// the resident solve below takes when no launch-shape option, profiling,
+// graph replay or the single-reduction form asks for the multi-workgroup
+// kernels; either way only if a 256-row tile fits in 64 KB.
 constexpr int64_t kOneAutoRows = 2048;  // measured crossover with the launch-per-iteration path
 
 // Without an explicit SPX_OPT_CG_VARIANT, systems of at most kSrAutoNnz
@@ -1189,8 +1190,12 @@ bool use_regs(const spx_matrix* h, const Csr& M) {
 
 // The resident solve (cg_grid.hip): any fp32 inner solve, and fp64 systems
 // above kGridFromRows, whose matrix fits the CUs' LDS, when no option asks
-// for a launch shape or another form of the recurrences than its own, the
-// single reduction.  Per fp64 iteration,
+// for a launch shape or a form that it is not meant for (the pipelined one,
+// and the textbook one asked for by number).  It takes the form that the solve
+// has without it, the single-reduction one below 2M entries except where the
+// one-workgroup solve would run, else the textbook one: 8.8 and 8.8 us an
+// iteration on 97,336 rows of 27 entries, 8.3 and 8.4 on 240,100 of 9, 9.2
+// and 9.3 on 410,881 of 5, 6.7 and 6.8 on 1,728 of 27.  Per fp64 iteration,
 // resident against what took the size before: 121 rows 5.8 us against 5.5
 // (one workgroup), 289 rows 5.0 / 5.5, 1,089 rows 4.7 / 9.8, 2,025 rows 4.8
 // / 13.1; 4,225 rows 5.0 / 13.5 (two launches), 66,049 rows 6.8 / 13.9,
@@ -1251,7 +1256,10 @@ int cg_solve_impl(spx_matrix* h, const Work& w, const Csr& M, const double* b, d
   }
   if (use_grid(h, M, false)) {
     bool launched = false;
-    SPX_TRY(launch_grid_cg(M, b, x, w.vec + 3 * n, w.partials, st, rtol, maxit, s, &launched));
+    // the form that the solve would take without it
+    const bool textbook = form == 0 || use_one_workgroup(h, M);
+    SPX_TRY(launch_grid_cg(M, textbook, b, x, w.vec + 3 * n, w.partials, st, rtol, maxit, s,
+                           &launched));
     if (launched) {
       const int rc = finish_solve(h, w, A, b, x, st, s, iters_out, relres_out);
       if (w.host[2].verify)

@@ -11,9 +11,11 @@
 // KB per workgroup, through memory) and three sums, so an iteration is two
 // exchanges between the resident workgroups.
 //
-// The recurrences, tests and statuses are those of the single-reduction
-// form in cg.hip (k_sr_update, k_sr_spmv), element by element; only the
-// order in which the dots' partial sums are added differs.
+// The recurrences, tests and statuses are those of the form in cg.hip that
+// the solve would take without this launch, the single-reduction one
+// (k_sr_update, k_sr_spmv) or the textbook one (k_cg_update, k_cg_pupdate),
+// element by element; only the order in which the dots' partial sums are
+// added differs.
 //
 // An exchange: each workgroup stores its partial sums in its slots, every
 // workgroup reads all slots and adds them in the same order, so all take
@@ -28,6 +30,7 @@
 // up, and the solve reports an error.
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "common.hpp"
 #include "device.hpp"
@@ -285,8 +288,10 @@ struct GridSolve {
 };
 
 // The fp64 solve.  Thread t owns rows r0 + t, r0 + t + kGridBlock, ... (RPT
-// of them).
-template <int RPT>
+// of them).  TEXTBOOK: that form, in which each workgroup keeps p on its whole
+// window, as k_cg_grid_inner does, so it takes two exchanges an iteration
+// too; s is then A p.
+template <int RPT, bool TEXTBOOK>
 __global__ __launch_bounds__(kGridBlock) void k_cg_grid(GridMat<double> A, GridSolve a) {
   extern __shared__ __align__(16) char smem[];
   __shared__ GridLds l;
@@ -341,7 +346,61 @@ __global__ __launch_bounds__(kGridBlock) void k_cg_grid(GridMat<double> A, GridS
     status = SPX_NOT_CONVERGED;
   else
     run = true;
-  if (run) {
+  // x, r and u with the iteration's alpha, and the sums of r.u and r.r
+  const auto update = [&]() {
+    gr[0] = gr[1] = 0.0;
+#pragma unroll
+    for (int q = 0; q < RPT; ++q) {
+      const int64_t row = S.r0 + tid + q * kGridBlock;
+      x[q] = x[q] + alpha * p[q];
+      r[q] = r[q] - alpha * s[q];
+      u[q] = dinv[q] * r[q];
+      if (row < S.r1) agent_store(a.u + row, u[q]);
+      gr[0] += r[q] * u[q];
+      gr[1] += r[q] * r[q];
+    }
+    return exchange(a.slots, ++number, l, gr);
+  };
+  if (TEXTBOOK && run) {
+    grid_window<true>(a.u, A.n, S, stage);
+#pragma unroll
+    for (int q = 0; q < RPT; ++q) p[q] = u[q];
+    for (int32_t k = 1;; ++k) {
+      double d[1] = {0.0};
+#pragma unroll
+      for (int q = 0; q < RPT; ++q) {
+        s[q] = grid_row(S, ra[q], re[q]);
+        d[0] += p[q] * s[q];
+      }
+      if (!exchange(a.slots, ++number, l, d)) {
+        status = kGridTimedOut;
+        break;
+      }
+      pq = d[0];
+      if (!(pq > 0.0) || !isfinite(pq)) {
+        status = SPX_BREAKDOWN;
+        iters = k - 1;
+        break;
+      }
+      alpha = gamma / pq;
+      if (!update()) {
+        status = kGridTimedOut;
+        break;
+      }
+      rr = gr[1];
+      iters = k;
+      if (sqrt(rr) <= thresh) break;
+      if (k >= a.maxit) {
+        status = SPX_NOT_CONVERGED;
+        break;
+      }
+      const double beta = gr[0] / gamma;
+      gamma = gr[0];
+#pragma unroll
+      for (int q = 0; q < RPT; ++q) p[q] = u[q] + beta * p[q];
+      grid_window<true>(a.u, A.n, S, [&](int i, double v) { S.xs[i] = v + beta * S.xs[i]; });
+    }
+  } else if (run) {
     double g_prev = 0.0;
     for (int32_t k = 0;; ++k) {
       // w = A u; p = u + beta p; s = w + beta s (p = u, s = w at k = 0)
@@ -366,18 +425,7 @@ __global__ __launch_bounds__(kGridBlock) void k_cg_grid(GridMat<double> A, GridS
         break;
       }
       alpha = gamma / pq;
-      gr[0] = gr[1] = 0.0;
-#pragma unroll
-      for (int q = 0; q < RPT; ++q) {
-        const int64_t row = S.r0 + tid + q * kGridBlock;
-        x[q] = x[q] + alpha * p[q];
-        r[q] = r[q] - alpha * s[q];
-        u[q] = dinv[q] * r[q];
-        if (row < S.r1) agent_store(a.u + row, u[q]);
-        gr[0] += r[q] * u[q];
-        gr[1] += r[q] * r[q];
-      }
-      if (!exchange(a.slots, ++number, l, gr)) {
+      if (!update()) {
         status = kGridTimedOut;
         break;
       }
@@ -391,6 +439,8 @@ __global__ __launch_bounds__(kGridBlock) void k_cg_grid(GridMat<double> A, GridS
         break;
       }
     }
+  }
+  if (run) {
 #pragma unroll
     for (int q = 0; q < RPT; ++q) {
       const int64_t row = S.r0 + tid + q * kGridBlock;
@@ -608,16 +658,21 @@ bool grid_cg_fits(const Csr& M, bool fp32) {
               : !M.grid_unfit && grid_plan<double>(M, &g);
 }
 
-int launch_grid_cg(const Csr& M, const double* b, double* x, double* u, double* slots,
-                   CgScalars* st, double rtol, int64_t maxit, hipStream_t s, bool* launched) {
+int launch_grid_cg(const Csr& M, bool textbook, const double* b, double* x, double* u,
+                   double* slots, CgScalars* st, double rtol, int64_t maxit, hipStream_t s,
+                   bool* launched) {
   *launched = false;
   GridPlan g;
   if (!grid_plan<double>(M, &g)) return SPX_OK;
   GridMat<double> A{M.n, M.rowptr, M.col, M.val, g.rows, g.entries, g.blocks};
   GridSolve a{M.dpos, b, x, u, reinterpret_cast<Pair*>(slots), st, rtol, (int32_t)maxit};
-  const void* fn = g.rpt == 1   ? reinterpret_cast<const void*>(&k_cg_grid<1>)
-                   : g.rpt == 2 ? reinterpret_cast<const void*>(&k_cg_grid<2>)
-                                : reinterpret_cast<const void*>(&k_cg_grid<kGridMaxRpt>);
+  auto form = [&](auto t) {
+    constexpr bool T = decltype(t)::value;
+    return g.rpt == 1   ? reinterpret_cast<const void*>(&k_cg_grid<1, T>)
+           : g.rpt == 2 ? reinterpret_cast<const void*>(&k_cg_grid<2, T>)
+                        : reinterpret_cast<const void*>(&k_cg_grid<kGridMaxRpt, T>);
+  };
+  const void* fn = textbook ? form(std::true_type()) : form(std::false_type());
   return grid_launch(g, fn, A, a, st, maxit, s, launched);
 }
 

@@ -312,8 +312,8 @@ int launch_spmm_rowset(const Csr& A, const double* X, double* Y, hipStream_t s);
 int launch_spmm_pattern(const Csr& A, int64_t nrhs, const double* X, int64_t ldx, double* Y,
                         int64_t ldy, hipStream_t s, bool* launched);
 // cg_grid.hip: a whole CG solve as one cooperative launch.  grid_cg_fits:
-// the pattern may take it.  launch_grid_cg: the fp64 solve with the work
-// vector u[n]; resets *st.  launch_grid_inner: the fp32 inner solve of the
+// the pattern may take it.  launch_grid_cg: the fp64 solve, in the textbook
+// form or the single-reduction one, with the work vector u[n]; resets *st.  launch_grid_inner: the fp32 inner solve of the
 // refinement, from the state k_ir_finish left in *st.  slots: kGridSlotWords
 // 8-byte words.  *launched is false when the device refused the launch.
 // Besides the solver's statuses st->status may come back as kGridUnfit
@@ -323,8 +323,9 @@ constexpr int kGridSlotWords = 16384;
 constexpr int32_t kGridUnfit = 1;
 constexpr int32_t kGridTimedOut = 2;
 bool grid_cg_fits(const Csr& M, bool fp32);
-int launch_grid_cg(const Csr& M, const double* b, double* x, double* u, double* slots,
-                   CgScalars* st, double rtol, int64_t maxit, hipStream_t s, bool* launched);
+int launch_grid_cg(const Csr& M, bool textbook, const double* b, double* x, double* u,
+                   double* slots, CgScalars* st, double rtol, int64_t maxit, hipStream_t s,
+                   bool* launched);
 int launch_grid_inner(const Csr& M, float* x, const float* r, float* z, const float* dinv,
                       double* slots, CgScalars* st, hipStream_t s, bool* launched);
 // cg.hip
