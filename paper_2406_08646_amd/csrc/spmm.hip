@@ -164,6 +164,7 @@ __global__ __launch_bounds__(kRsBlock) void k_rs_build(int64_t n, const int32_t*
 constexpr int kRpLanes = 16;
 constexpr int kRpRow = kRpLanes * 8;  // bytes of a row of X
 typedef double rs_d2 __attribute__((ext_vector_type(2)));
+typedef rs_d2 rs_d2u __attribute__((aligned(8)));  // at any column
 
 template <int J>
 __device__ __forceinline__ int rs_bcast(int v) {
@@ -554,9 +555,16 @@ struct SpmmForm {
   static_assert(lds * PER_CU <= 160 * 1024, "the workgroups of a CU fit its LDS");
 };
 
-// A16: X and Y are 16-byte aligned with even strides.  A column past the last
-// is the last again, and is not stored.
-template <class F, bool A16>
+// Columns are loaded by 16 bytes (PAIRS not 0) where X and Y are 16-byte
+// aligned with even strides and nrhs > 1.  A column past the last is not
+// stored; its loads take the columns before it.  ODD, where nrhs is: so the
+// last column is the second of its pair (the last row of X may end there) and
+// is turned round on its way to LDS.  (By 8-byte loads for all of X 5 columns of
+// stride 6 took 52 us against 50 on 1001^2 rows of 5 points, 23 of stride 24
+// 593 against 535 on 111^3 rows of 27; the turn spills a little in the lean
+// form, where even widths go without it: 6 columns 45 us, 47 with it.)
+enum { SCALAR, EVEN, ODD };
+template <class F, int PAIRS>
 __global__ __launch_bounds__(F::threads, F::per_cu * F::q) void k_spmm_pattern(
     int64_t n, const int32_t* __restrict__ rowptr, const double* __restrict__ val, int nrhs,
     const double* __restrict__ X, int64_t ldx, double* __restrict__ Y, int64_t ldy, WinView w) {
@@ -601,8 +609,10 @@ __global__ __launch_bounds__(F::threads, F::per_cu * F::q) void k_spmm_pattern(
       } else {
         px = X + min((int64_t)bq[i] * kWinBlock + slot, n - 1) * ldx;
       }
-      if constexpr (A16)
-        xr[i] = *reinterpret_cast<const rs_d2*>(px + min(c, (nrhs - 1) & ~1));
+      if constexpr (PAIRS == EVEN)
+        xr[i] = *reinterpret_cast<const rs_d2*>(px + min(c, nrhs - 2));
+      else if constexpr (PAIRS == ODD)
+        xr[i] = *reinterpret_cast<const rs_d2u*>(px + min(c, nrhs - 2));
       else
         xr[i] = rs_d2{px[ca], px[cb]};
     }
@@ -637,7 +647,10 @@ __global__ __launch_bounds__(F::threads, F::per_cu * F::q) void k_spmm_pattern(
       if (u * T + tid < kV) vals[u * T + tid] = a[u];
     for (int c0 = 0, panel = 0; panel < panels; ++panel, c0 += 2 * Q) {
 #pragma unroll
-      for (int i = 0; i < PRE; ++i) xs[((wv / Q + 4 * i) * kWinBlock + slot) * Q + xq] = xr[i];
+      for (int i = 0; i < PRE; ++i) {
+        if constexpr (PAIRS == ODD) xr[i].x = c0 + 2 * xq == nrhs - 1 ? xr[i].y : xr[i].x;
+        xs[((wv / Q + 4 * i) * kWinBlock + slot) * Q + xq] = xr[i];
+      }
       if (panel + 1 < panels) {
         issue_x(c0 + 2 * Q);
       } else if (next < tiles) {
@@ -667,7 +680,7 @@ __global__ __launch_bounds__(F::threads, F::per_cu * F::q) void k_spmm_pattern(
       const int c = c0 + 2 * q;
       if (row < n && c < nrhs) {
         double* py = Y + row * ldy + c;
-        if (A16 && c + 1 < nrhs) {
+        if (PAIRS == EVEN || (PAIRS == ODD && c + 1 < nrhs)) {
           *reinterpret_cast<rs_d2*>(py) = s;
         } else {
           py[0] = s.x;
@@ -756,7 +769,8 @@ int launch_spmm_pattern(const Csr& A, int64_t nrhs, const double* X, int64_t ldx
       *launched = true;
       return SPX_OK;
     };
-    return a16 ? run(&k_spmm_pattern<F, true>) : run(&k_spmm_pattern<F, false>);
+    if (!a16 || nrhs == 1) return run(&k_spmm_pattern<F, SCALAR>);
+    return nrhs % 2 ? run(&k_spmm_pattern<F, ODD>) : run(&k_spmm_pattern<F, EVEN>);
   };
   // threads per row: as few panels as fit the LDS, equally wide
   const int64_t pairs = ceil_div(nrhs, 2), most_q = blocks <= 24 ? 4 : 3;
