@@ -1262,6 +1262,7 @@ int cg_solve_impl(spx_matrix* h, const Work& w, const Csr& M, const double* b, d
                            &launched));
     if (launched) {
       const int rc = finish_solve(h, w, A, b, x, st, s, iters_out, relres_out);
+      if (rc == SPX_HIP_ERROR) return rc;  // host[2] is not this solve's
       if (w.host[2].verify)
         return set_error(SPX_HIP_ERROR, "cg_solve: the workgroups of the resident solve lost step");
       if (w.host[2].status != kGridUnfit) return rc;
@@ -1359,6 +1360,7 @@ int cg_solve_impl(spx_matrix* h, const Work& w, const Csr& M, const double* b, d
 }
 
 // True residual of the returned x, the outputs and the status of a solve.
+// SPX_HIP_ERROR only where w.host[2] did not receive the solve's scalars.
 int finish_solve(spx_matrix* h, const Work& w, const Op<double>& A, const double* b,
                  const double* x, CgScalars* st, hipStream_t s, int64_t* iters_out,
                  double* relres_out) {
@@ -1633,7 +1635,7 @@ extern "C" int spx_cg_solve_noalloc(spx_handle h, const double* b, double* x, do
   w.partials = base + kScratchScal;
   w.vec = w.partials + kScratchPartials;
   w.dinv = w.vec + 4 * kScratchStride;
-  CgScalars host[4];  // pageable: read only after the stream is synchronised
+  CgScalars host[4] = {};  // pageable: read only after the stream is synchronised
   w.host = host;
   w.ev = nullptr;
   return cg_solve_impl(h, w, h->A, b, x, rtol, maxit, check_every,
