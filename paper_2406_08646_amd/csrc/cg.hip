@@ -774,7 +774,9 @@ int ensure_solver32(spx_matrix* h) {
 struct Work {
   double* vec = nullptr;       // [4 n], [9 n] for the pipelined form
   double* dinv = nullptr;      // [n]
-  double* partials = nullptr;  // [6 max(fused_blocks, vector_blocks)]
+  // [max(p max(fused_blocks, vector_blocks), kGridSlotWords)], p = 4 (6 for
+  // the pipelined form)
+  double* partials = nullptr;
   CgScalars* scal = nullptr;   // device [2]
   CgScalars* host = nullptr;   // host [4]
   const hipEvent_t* ev = nullptr;  // 2 events or null
@@ -1568,6 +1570,8 @@ namespace {
 constexpr int64_t kNoallocMaxBlocks = 4096;  // workgroups of a solver kernel
 constexpr int64_t kScratchScal = 2 * ((sizeof(CgScalars) + 255) / 256) * 32;
 constexpr int64_t kScratchPartials = 4 * kNoallocMaxBlocks;
+static_assert(kScratchPartials >= kGridSlotWords, "the resident solve's slots fit the partials");
+static_assert(kScratchPartials % 32 == 0, "the vectors after them stay 256-byte aligned");
 constexpr int64_t kScratchStride = (SPX_NOALLOC_MAX_ROWS + 31) / 32 * 32;
 constexpr int64_t kScratchDoubles = kScratchScal + kScratchPartials + 5 * kScratchStride;
 constexpr int kScratchDevices = 64;
