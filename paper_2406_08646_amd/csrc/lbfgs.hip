@@ -239,6 +239,8 @@ __global__ __launch_bounds__(kLB) void k_lb_ya(int64_t n, int64_t tiles,
 #pragma unroll
     for (int q = 0; q < kWaves; ++q) a += part[buf][q][lane];
     if constexpr (H0) a = hv * a;
+    // no row at n and beyond: 0 times an infinite c is not 0
+    a = dbl2{r < n ? a.x : 0.0, r + 1 < n ? a.y : 0.0};
     // a place of hold belongs to one wave, which fills and empties it
     if (w == (held & (kWaves - 1))) hold[held][lane] = a;
     if (++held == kHold || t + gridDim.x >= tiles) {
