@@ -346,21 +346,6 @@ __global__ __launch_bounds__(kGridBlock) void k_cg_grid(GridMat<double> A, GridS
     status = SPX_NOT_CONVERGED;
   else
     run = true;
-  // x, r and u with the iteration's alpha, and the sums of r.u and r.r
-  const auto update = [&]() {
-    gr[0] = gr[1] = 0.0;
-#pragma unroll
-    for (int q = 0; q < RPT; ++q) {
-      const int64_t row = S.r0 + tid + q * kGridBlock;
-      x[q] = x[q] + alpha * p[q];
-      r[q] = r[q] - alpha * s[q];
-      u[q] = dinv[q] * r[q];
-      if (row < S.r1) agent_store(a.u + row, u[q]);
-      gr[0] += r[q] * u[q];
-      gr[1] += r[q] * r[q];
-    }
-    return exchange(a.slots, ++number, l, gr);
-  };
   if (TEXTBOOK && run) {
     grid_window<true>(a.u, A.n, S, stage);
 #pragma unroll
@@ -383,7 +368,18 @@ __global__ __launch_bounds__(kGridBlock) void k_cg_grid(GridMat<double> A, GridS
         break;
       }
       alpha = gamma / pq;
-      if (!update()) {
+      gr[0] = gr[1] = 0.0;
+#pragma unroll
+      for (int q = 0; q < RPT; ++q) {
+        const int64_t row = S.r0 + tid + q * kGridBlock;
+        x[q] = x[q] + alpha * p[q];
+        r[q] = r[q] - alpha * s[q];
+        u[q] = dinv[q] * r[q];
+        if (row < S.r1) agent_store(a.u + row, u[q]);
+        gr[0] += r[q] * u[q];
+        gr[1] += r[q] * r[q];
+      }
+      if (!exchange(a.slots, ++number, l, gr)) {
         status = kGridTimedOut;
         break;
       }
@@ -425,7 +421,18 @@ __global__ __launch_bounds__(kGridBlock) void k_cg_grid(GridMat<double> A, GridS
         break;
       }
       alpha = gamma / pq;
-      if (!update()) {
+      gr[0] = gr[1] = 0.0;
+#pragma unroll
+      for (int q = 0; q < RPT; ++q) {
+        const int64_t row = S.r0 + tid + q * kGridBlock;
+        x[q] = x[q] + alpha * p[q];
+        r[q] = r[q] - alpha * s[q];
+        u[q] = dinv[q] * r[q];
+        if (row < S.r1) agent_store(a.u + row, u[q]);
+        gr[0] += r[q] * u[q];
+        gr[1] += r[q] * r[q];
+      }
+      if (!exchange(a.slots, ++number, l, gr)) {
         status = kGridTimedOut;
         break;
       }
