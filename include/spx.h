@@ -550,7 +550,9 @@ int spx_set_allocator(spx_alloc_fn alloc, spx_free_fn free, void* ctx);
  *     up to 2048 rows with SPX_OPT_CG_VARIANT -1, else that option's.  So
  *     are the fp32 inner solves of spx_cg_solve_mixed (about 6 bytes per
  *     entry); 0 keeps both to launches per iteration.  A pattern whose rows
- *     need too much of x per workgroup takes those as well.
+ *     need too much of x per workgroup takes those as well, and so does one
+ *     whose first launch the device refused (while another process holds
+ *     its queue for cooperative launches), for as long as it lives.
  *   SPX_OPT_IR_EARLY_EXIT: inner stopping rule of spx_cg_solve_mixed.
  *     0 (default): each inner solve runs to rtol_inner relative to its
  *     right-hand side.  1: it also stops once its residual is at most

@@ -1268,9 +1268,9 @@ int cg_solve_impl(spx_matrix* h, const Work& w, const Csr& M, const double* b, d
       if (w.host[2].verify)
         return set_error(SPX_HIP_ERROR, "cg_solve: the workgroups of the resident solve lost step");
       if (w.host[2].status != kGridUnfit) return rc;
-      M.grid_unfit = true;  // the pattern's, kept with it: not tried again
       clear_error();
     }
+    M.grid_unfit = true;  // the pattern's, kept with it: not tried again
   }
   hipLaunchKernelGGL(k_scal_reset, dim3(1), dim3(64), 0, s, st, (int32_t)maxit);
   hipLaunchKernelGGL(k_dinv, dim3(grid1(n)), dim3(256), 0, s, n, M.val, M.dpos, w.dinv,
@@ -1522,12 +1522,12 @@ extern "C" int spx_cg_solve_mixed(spx_handle h, const double* b, double* x, doub
           return set_error(SPX_HIP_ERROR,
                            "cg_solve_mixed: the workgroups of the resident solve lost step");
         if (fin.status == kGridUnfit) {
-          // the pattern's, kept with it; the launches below take this solve
-          M.grid_unfit32 = true;
           resident = false;
           hipLaunchKernelGGL(k_resume, dim3(1), dim3(64), 0, s, si);
         }
       }
+      // the pattern's, kept with it; the launches below take this solve
+      if (!resident) M.grid_unfit32 = true;
     }
     if (!resident)
       SPX_TRY(run_hs<float>(h, w, A32, d32, r32, p32, q32, h->dinv32, si, maxit_inner, check_every,

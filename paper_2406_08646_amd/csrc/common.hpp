@@ -151,7 +151,8 @@ struct Csr {
   int64_t tile_nnz[4] = {0, 0, 0, 0};
   Window win;  // empty (lcol == nullptr) when the pattern does not profit from one
   RowSet rs;   // built on the first 16-column product
-  // the pattern's rows do not fit the resident solve's LDS (cg_grid.hip)
+  // the resident solve (cg_grid.hip) is not for this pattern: its rows do not
+  // fit the LDS, or the device refused the launch
   mutable bool grid_unfit = false, grid_unfit32 = false;
 };
 
@@ -315,7 +316,9 @@ int launch_spmm_pattern(const Csr& A, int64_t nrhs, const double* X, int64_t ldx
 // the pattern may take it.  launch_grid_cg: the fp64 solve, in the textbook
 // form or the single-reduction one, with the work vector u[n]; resets *st.  launch_grid_inner: the fp32 inner solve of the
 // refinement, from the state k_ir_finish left in *st.  slots: kGridSlotWords
-// 8-byte words.  *launched is false when the device refused the launch.
+// 8-byte words.  *launched is false when the device refused the launch (its
+// queue for cooperative launches serves one process at a time); asking costs
+// 40 ms then, so a pattern asks once.
 // Besides the solver's statuses st->status may come back as kGridUnfit
 // (nothing solved, no vector changed), and st->verify as 1 when a wait
 // between workgroups gave up.
