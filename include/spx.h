@@ -566,7 +566,14 @@ int spx_set_allocator(spx_alloc_fn alloc, spx_free_fn free, void* ctx);
  *     pipelined: two LDS buffers per workgroup, the next tile's rows of X
  *     loading while the current tile's products are formed).  The tiles'
  *     index is rebuilt on the next product after a change.  Results are the
- *     same bits at every height. */
+ *     same bits at every height.
+ *   SPX_OPT_ROW_PATTERNS (read only): 1 where MatMult walks A by row patterns
+ *     and reads no columns (see SPX_OPT_SPMV_VARIANT), else 0.
+ *   SPX_OPT_LAST_SOLVE (read only): what ran the last solve of any kind with
+ *     this matrix, its transpose or a batch that holds it: 0 nothing yet, 1
+ *     launches per iteration, 2 one workgroup that walks memory, 3 one that
+ *     holds the system in registers, 4 one cooperative launch (for
+ *     spx_cg_solve_mixed: the inner solves). */
 enum spx_option {
   SPX_OPT_SPMV_LANES = 1,
   SPX_OPT_XCD_REMAP = 2,
@@ -583,7 +590,9 @@ enum spx_option {
   SPX_OPT_GRAPH = 13,
   SPX_OPT_SMALL_SOLVE = 14,
   SPX_OPT_IR_EARLY_EXIT = 15,
-  SPX_OPT_SPMM_TILE_ROWS = 16
+  SPX_OPT_SPMM_TILE_ROWS = 16,
+  SPX_OPT_ROW_PATTERNS = 17,
+  SPX_OPT_LAST_SOLVE = 18
 };
 int spx_set_option(spx_handle h, int32_t option, int64_t value);
 int spx_get_option(spx_handle h, int32_t option, int64_t* value);

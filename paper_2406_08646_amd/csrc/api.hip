@@ -234,6 +234,9 @@ extern "C" int spx_set_option(spx_handle h, int32_t option, int64_t value) {
         return set_error(SPX_INVALID_ARG, "set_option: SpMM tile height must be 0, 16, 32 or 64");
       h->spmm_rows_opt = (int)value;
       return SPX_OK;
+    case SPX_OPT_ROW_PATTERNS:
+    case SPX_OPT_LAST_SOLVE:
+      return set_error(SPX_INVALID_ARG, "set_option: option %d is read only", option);
     default:
       return set_error(SPX_INVALID_ARG, "set_option: unknown option %d", option);
   }
@@ -290,6 +293,14 @@ extern "C" int spx_get_option(spx_handle h, int32_t option, int64_t* value) {
       return SPX_OK;
     case SPX_OPT_SPMM_TILE_ROWS:
       *value = h->spmm_rows_opt ? h->spmm_rows_opt : 32;
+      return SPX_OK;
+    case SPX_OPT_ROW_PATTERNS: {
+      const SpmvShape sh = matmult_shape(h, h->A);
+      *value = walks_patterns(h->A, sh, remap_for(h, sh)) ? 1 : 0;
+      return SPX_OK;
+    }
+    case SPX_OPT_LAST_SOLVE:
+      *value = h->last_solve.load(std::memory_order_relaxed);
       return SPX_OK;
     default:
       return set_error(SPX_INVALID_ARG, "get_option: unknown option %d", option);

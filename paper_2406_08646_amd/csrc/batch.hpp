@@ -81,6 +81,11 @@ struct spx_batch {
 namespace spx {
 namespace batch {
 
+// Notes what runs a solve of the batch in its systems' handles.
+inline void note_solve(const spx_batch* B, SolveKind kind) {
+  for (spx_handle h : B->hs) h->last_solve.store(kind, std::memory_order_relaxed);
+}
+
 // Splits G workgroups among the active systems: team size proportional to
 // nnz_s^gamma, at least one workgroup each, teams contiguous in system order.
 inline void make_plan(const spx_batch* B, const std::vector<char>& active, int G, double gamma,

@@ -435,7 +435,9 @@ extern "C" int spx_batch_cg(spx_batch_handle B, const double* bvec, double* x, d
                        (int32_t)maxit);
     hipLaunchKernelGGL(k_b_queue_reset, dim3(1), dim3(64), 0, s, B->d_queue);
     int held = SPX_OK;
-    if (regs_persistent(B, ps, bvec, x, rtol, s, &held))
+    const bool regs = regs_persistent(B, ps, bvec, x, rtol, s, &held);
+    note_solve(B, regs ? kHeldInRegisters : kOneWorkgroup);
+    if (regs)
       SPX_TRY(held);
     else if (ps.block == 256)
       SPX_TRY((launch_persistent<256, 256>(B, ps, bvec, x, r, p, q, dinv, rtol, s)));
@@ -449,6 +451,7 @@ extern "C" int spx_batch_cg(spx_batch_handle B, const double* bvec, double* x, d
     SPX_TRY(true_residuals(B, run, bvec, x, s));
     return finish(B, s, iters_out, relres_out, "batch_cg");
   }
+  note_solve(B, kByLaunches);
   double* P1 = B->partials;
   double* P2 = B->partials + G;
   const PlanView pl = run.pl;

@@ -650,7 +650,9 @@ int maybe_persistent(spx_batch* B, const spx_batch_tuning* tuning, int64_t tile2
   int32_t mode = 0;
   SPX_TRY(persistent_mode(tuning, what, &mode));
   const PersistShape ps = persistent_shape(B, tile256);
-  if (!(mode == 1 || (mode == 0 && persistent_by_default(B, ps)))) return SPX_OK;
+  const bool take = mode == 1 || (mode == 0 && persistent_by_default(B, ps));
+  note_solve(B, take ? kOneWorkgroup : kByLaunches);
+  if (!take) return SPX_OK;
   if (ps.lds == 0)
     return set_error(SPX_INVALID_ARG,
                      "%s: a 256-row tile of a system exceeds the persistent solve's LDS", what);

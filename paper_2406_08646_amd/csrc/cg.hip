@@ -1254,6 +1254,7 @@ int cg_solve_impl(spx_matrix* h, const Work& w, const Csr& M, const double* b, d
     else
       go(k_cg_regs<512, 4, 9>, 512);
     SPX_CHECK_HIP(hipGetLastError());
+    h->last_solve.store(kHeldInRegisters, std::memory_order_relaxed);
     return finish_solve(h, w, A, b, x, st, s, iters_out, relres_out);
   }
   if (use_grid(h, M, false)) {
@@ -1267,11 +1268,16 @@ int cg_solve_impl(spx_matrix* h, const Work& w, const Csr& M, const double* b, d
       if (rc == SPX_HIP_ERROR) return rc;  // host[2] is not this solve's
       if (w.host[2].verify)
         return set_error(SPX_HIP_ERROR, "cg_solve: the workgroups of the resident solve lost step");
-      if (w.host[2].status != kGridUnfit) return rc;
+      if (w.host[2].status != kGridUnfit) {
+        h->last_solve.store(kCooperative, std::memory_order_relaxed);
+        return rc;
+      }
       clear_error();
     }
     M.grid_unfit = true;  // the pattern's, kept with it: not tried again
   }
+  h->last_solve.store(form != 2 && use_one_workgroup(h, M) ? kOneWorkgroup : kByLaunches,
+                      std::memory_order_relaxed);
   hipLaunchKernelGGL(k_scal_reset, dim3(1), dim3(64), 0, s, st, (int32_t)maxit);
   hipLaunchKernelGGL(k_dinv, dim3(grid1(n)), dim3(256), 0, s, n, M.val, M.dpos, w.dinv,
                      (float*)nullptr, st);
@@ -1529,6 +1535,7 @@ extern "C" int spx_cg_solve_mixed(spx_handle h, const double* b, double* x, doub
       // the pattern's, kept with it; the launches below take this solve
       if (!resident) M.grid_unfit32 = true;
     }
+    h->last_solve.store(resident ? kCooperative : kByLaunches, std::memory_order_relaxed);
     if (!resident)
       SPX_TRY(run_hs<float>(h, w, A32, d32, r32, p32, q32, h->dinv32, si, maxit_inner, check_every,
                             s, &fin));

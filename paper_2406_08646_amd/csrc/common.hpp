@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cstddef>
 #include <cstdint>
 
@@ -198,6 +199,9 @@ struct CgScalars {
   int32_t kcur;
 };
 
+// What ran a solve (SPX_OPT_LAST_SOLVE).
+enum SolveKind : int32_t { kByLaunches = 1, kOneWorkgroup, kHeldInRegisters, kCooperative };
+
 }  // namespace spx
 
 struct spx_matrix {
@@ -245,6 +249,7 @@ struct spx_matrix {
   int small_opt = 1;  // one-workgroup solve: 0 never, 1 small systems, 2 whenever it fits
   int ir_early_exit = 0;  // refinement: 1 also ends an inner solve at rtol_outer ||b|| / 2
   int spmm_rows_opt = 0;  // tile height of the staged 16-column product, 0 = 32
+  std::atomic<int32_t> last_solve{0};  // SolveKind; batches that share the handle set it too
   hipStream_t cap_stream = nullptr;
   struct GraphCache {
     hipGraphExec_t exec = nullptr;
@@ -296,6 +301,8 @@ SpmvShape spmv_shape32(const spx_matrix* h, const Csr& A);
 SpmvShape solver_shape(const spx_matrix* h, const Csr& A);
 int launch_spmv(const Csr& A, const SpmvShape& sh, const double* x, double* y, int remap,
                 hipStream_t s);
+// A is walked by row patterns in shape sh with block order remap
+bool walks_patterns(const Csr& A, const SpmvShape& sh, int remap);
 int launch_spmm(const Csr& A, int64_t nrhs, const double* X, int64_t ldx, double* Y, int64_t ldy,
                 hipStream_t s);
 // Raises a kernel's LDS limit where it needs that.

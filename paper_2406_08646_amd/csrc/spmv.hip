@@ -618,23 +618,31 @@ SpmvShape solver_shape(const spx_matrix* h, const Csr& A) {
   return sh;
 }
 
+bool walks_patterns(const Csr& A, const SpmvShape& sh, int remap) {
+  // the pattern walk has no other loads and order
+  if (sh.variant != kVariantWindow || !sh.nt || remap) return false;
+  bool form = false;
+  (void)with_pattern<double>(A, [&](auto) {
+    form = true;
+    return SPX_OK;
+  });
+  return form;
+}
+
 int launch_spmv(const Csr& A, const SpmvShape& sh, const double* x, double* y, int remap,
                 hipStream_t s) {
   if (A.n == 0) return SPX_OK;
   if (sh.variant == kVariantWindow) {
     const int64_t nb = ceil_div(A.n, kWinRows);
-    if (sh.nt && !remap) {  // the pattern walk has no other loads and order
-      bool launched = false;
-      SPX_TRY(with_pattern<double>(A, [&](auto p) -> int {
+    if (walks_patterns(A, sh, remap)) {
+      return with_pattern<double>(A, [&](auto p) -> int {
         using P = decltype(p);
         const size_t bytes = pattern_lds_bytes<P, double>();
         SPX_TRY(allow_lds(reinterpret_cast<const void*>(&k_spmv_pattern<P>), bytes));
         hipLaunchKernelGGL(k_spmv_pattern<P>, dim3(pattern_blocks<P>(nb)), dim3(kWinRows), bytes, s,
                            A.n, A.rowptr, A.val, x, y, win_view(A));
-        launched = true;
         return SPX_OK;
-      }));
-      if (launched) return SPX_OK;
+      });
     }
     const size_t lds =
         window_lds_bytes(A.win.max_blocks, sizeof(double), kWinUProduct * win_v<double>());

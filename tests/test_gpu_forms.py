@@ -1,0 +1,136 @@
+"""Which kernels the default calls reach (the results alone cannot tell: every
+form falls back silently to one with the same bits or the same tolerance):
+products by row patterns and just past them, solves held in registers, by one
+workgroup, by one cooperative launch and by launches per iteration."""
+import numpy as np
+import pytest
+
+from paper_2406_08646_amd import workloads as W
+from gpu_util import assemble, bits, dev, host, require_gpu
+from test_gpu_cg_held import five_point as held_five_point, q1, seven_point
+from test_gpu_cg_resident import five_point, scattered
+from test_gpu_patterns import CASES
+
+pytestmark = pytest.mark.gpu
+
+LAUNCHES, ONE_WORKGROUP, HELD, COOPERATIVE = 1, 2, 3, 4
+
+
+# rows past 32 entries; more than 16 lists in a tile (lists15 and 16 and the
+# long rows with those that the matrix's edge cuts off); windows past 32
+# blocks; an index that does not pay
+WITHOUT = {"length27", "length28", "length32", "length33", "lists15", "lists16", "lists17",
+           "lists40", "groups7", "groups8", "row1"}
+
+
+@pytest.mark.parametrize("case", sorted(CASES))
+def test_products_by_row_patterns(case):
+    spx = require_gpu()
+    A = assemble(spx, CASES[case]())
+    A.set_option(spx.OPT_SPMV_VARIANT, 4)
+    assert (A.get_option(spx.OPT_SPMV_VARIANT) == 4) == (case != "row1")
+    assert A.get_option(spx.OPT_ROW_PATTERNS) == (0 if case in WITHOUT else 1)
+    A.set_option(spx.OPT_NONTEMPORAL, 0)
+    assert A.get_option(spx.OPT_ROW_PATTERNS) == 0
+    for option in (spx.OPT_ROW_PATTERNS, spx.OPT_LAST_SOLVE):
+        with pytest.raises(spx.SpxError) as e:
+            A.set_option(option, 1)
+        assert e.value.code == spx.INVALID_ARG
+
+
+def whole_lists(n, lists, seed):
+    """Row r has the columns base(r) + lists[r % len(lists)], all of them in
+    range, so every tile has exactly those lists."""
+    width = 1 + max(max(o) for o in lists)
+    base = np.clip(np.arange(n) - width // 2, 0, n - width)
+    i = np.concatenate([np.full(len(lists[r % len(lists)]), r) for r in range(n)])
+    j = np.concatenate([base[r] + np.asarray(lists[r % len(lists)]) for r in range(n)])
+    v = np.random.default_rng(seed).uniform(-1, 1, i.size)
+    return W.CooProblem(n=n, i=i.astype(np.int32), j=j.astype(np.int32), v=v)
+
+
+LIMITS = {  # the longest lists, the fullest tiles (7167 entries) and the most lists, and past each
+    "full27": ([range(27)], 1), "full28": ([range(28)], 0),
+    "mixed32": ([range(32), range(23)], 1), "mixed33": ([range(33), range(22)], 0),
+    "lists15": ([[0, 1, 2 + k] for k in range(15)], 1),
+    "lists16": ([[0, 1, 2 + k] for k in range(16)], 1),
+    "lists17": ([[0, 1, 2 + k] for k in range(17)], 0)}
+
+
+@pytest.mark.parametrize("case", sorted(LIMITS))
+def test_whole_lists_at_the_limits(orc, case):
+    """Form and bits of both products."""
+    spx = require_gpu()
+    lists, patterned = LIMITS[case]
+    prob = whole_lists(2100, [list(o) for o in lists], 3)
+    A = assemble(spx, prob)
+    A.set_option(spx.OPT_SPMV_VARIANT, 4)
+    assert A.get_option(spx.OPT_SPMV_VARIANT) == 4
+    assert A.get_option(spx.OPT_ROW_PATTERNS) == patterned
+    ref = orc.assemble(prob.n, prob.i, prob.j, prob.v)
+    x = np.random.default_rng(4).uniform(-1, 1, prob.n)
+    x[700] = np.inf
+    for y, want in ((A.matmult(dev(x)), orc.spmv(ref, x)),
+                    (A.matmult_transpose(dev(x)), orc.spmv_transpose(ref, x))):
+        y = host(y)
+        assert np.array_equal(np.isnan(y), np.isnan(want))
+        ok = ~np.isnan(y)
+        assert np.array_equal(bits(y[ok]), bits(want[ok]))
+
+
+@pytest.mark.parametrize("case", [17, 36, 64, 181, 363, 513, "scattered"])
+def test_mid_size_solves_are_one_launch(case):
+    """The systems of the resident solve's tests: up to 2048 rows of 5 entries
+    the registers hold them, the scattered pattern's windows do not fit."""
+    spx = require_gpu()
+    prob, b, _ = scattered(60000, 5) if case == "scattered" else five_point(case, case)
+    A, b = assemble(spx, prob), dev(b)
+    assert A.get_option(spx.OPT_LAST_SOLVE) == 0
+    want = LAUNCHES if case == "scattered" else HELD if prob.n <= 2048 else COOPERATIVE
+    for solve in (A.cg_solve, A.cg_solve_transpose):
+        solve(b, rtol=1e-3)
+        assert A.get_option(spx.OPT_LAST_SOLVE) == want
+    A.cg_solve_noalloc(b, x=dev(np.zeros(prob.n)), rtol=1e-3)
+    assert A.get_option(spx.OPT_LAST_SOLVE) == want
+    A.cg_solve_mixed(b, rtol_outer=1e-3)
+    assert A.get_option(spx.OPT_LAST_SOLVE) == (LAUNCHES if case == "scattered" else COOPERATIVE)
+    A.set_option(spx.OPT_SMALL_SOLVE, 0)
+    for solve in (A.cg_solve, A.cg_solve_mixed):
+        solve(b)
+        assert A.get_option(spx.OPT_LAST_SOLVE) == LAUNCHES
+
+
+@pytest.mark.parametrize("N,dim,want", [(5, 3, HELD), (6, 3, COOPERATIVE), (45, 3, COOPERATIVE),
+                                        (44, 2, HELD), (489, 2, COOPERATIVE), (60, 3, LAUNCHES)])
+def test_solves_by_size_and_row_length(N, dim, want):
+    spx = require_gpu()
+    prob = W.q1_poisson(N, dim)
+    A, b = assemble(spx, prob), dev(np.ones(prob.n))
+    A.cg_solve(b, rtol=1e-2)
+    assert A.get_option(spx.OPT_LAST_SOLVE) == want
+    if want == HELD:
+        A.set_option(spx.OPT_SMALL_SOLVE, 2)
+        A.cg_solve(b, rtol=1e-2)
+        assert A.get_option(spx.OPT_LAST_SOLVE) == ONE_WORKGROUP
+
+
+# the held batches of test_gpu_cg_held.py, then systems just past them
+@pytest.mark.parametrize("kind,sides,want", [
+    ("five", [1, 2, 16, 31, 32], HELD), ("q2", [1, 5, 15, 16, 31], HELD),
+    ("q3", [1, 2, 6, 9], HELD), ("five", [3, 33, 45, 63, 64], HELD),
+    ("seven", [2, 11, 15, 16], HELD), ("five", [32, 65, 72, 78], HELD),
+    ("five", [32, 79], ONE_WORKGROUP), ("seven", [2, 17], ONE_WORKGROUP),
+    ("q2", [5, 40], ONE_WORKGROUP)])
+def test_held_batches(kind, sides, want):
+    spx = require_gpu()
+    rng = np.random.default_rng(1)
+    make = {"five": lambda L: held_five_point(L, rng), "seven": lambda L: seven_point(L, rng),
+            "q2": lambda L: q1(L, 2, rng), "q3": lambda L: q1(L, 3, rng)}[kind]
+    systems = [assemble(spx, make(L)) for L in sides]
+    batch = spx.batch_create(systems)
+    b = dev(rng.uniform(-1, 1, batch.total))
+    for solve, form, got in ((batch.batch_cg, 1, want), (batch.batch_cg, -1, LAUNCHES),
+                             (batch.batch_bicg, 1, ONE_WORKGROUP),
+                             (batch.batch_tfqmr, -1, LAUNCHES)):
+        solve(b, rtol=1e-2, persistent=form)
+        assert all(A.get_option(spx.OPT_LAST_SOLVE) == got for A in systems)
