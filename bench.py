@@ -892,6 +892,7 @@ def main() -> int:
         A.set_option(spx.OPT_IR_EARLY_EXIT, 0)
         nnz = A.nnz
         rec["walk"] = A.get_option(spx.OPT_SPMV_VARIANT)
+        rec["patterns"] = A.get_option(spx.OPT_ROW_PATTERNS)
         rec["window"] = A.get_window(arrays=False)
         A.destroy()
         torch.cuda.synchronize()
@@ -941,12 +942,15 @@ def main() -> int:
 
     nnz = recs[0]["nnz"]
     mv_bytes = spmv_bytes(n, nnz)
-    walk = recs[0]["walk"]
+    walk, patterns = recs[0]["walk"], recs[0]["patterns"]
     # bytes of the format the walk reads; the staged x blocks are counted once
     # in x (they come through L2 for the neighbouring tiles)
-    # the window walk by row patterns: the values alone, 4 bytes a row and a
-    # 1 KB share of the lists per 256-row tile
-    fmt_bytes = mv_bytes - 4 * nnz + 4 * n + 1024 * ((n + 255) // 256) if walk == 4 else mv_bytes
+    if patterns:  # the values alone, 4 bytes a row and 1 KB of lists per 256-row tile
+        fmt_bytes = mv_bytes - 4 * nnz + 4 * n + 1024 * ((n + 255) // 256)
+    elif walk == 4:  # 16-bit window columns and the tiles' block lists
+        fmt_bytes = mv_bytes - 2 * nnz + 4 * recs[0]["window"]["total_blocks"]
+    else:
+        fmt_bytes = mv_bytes
     mv = [t for r in recs for t in r["spmv_ms"]]
     mvt = [t for r in recs for t in r["spmvt_ms"]]
     mv_med = statistics.median(mv)
@@ -1006,7 +1010,7 @@ def main() -> int:
         out["roofline"] = {
             "bound": "hbm", "achieved": round(ach, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",
             "frac": round(ach / PEAK_HBM_GBS, 4), "traffic": measured_traffic(),
-            "kernel": (f"{'k_cg_pattern' if walk == 4 else 'k_cg_spmv'} "
+            "kernel": (f"{'k_cg_pattern' if patterns else 'k_cg_spmv'} "
                        f"({WALKS.get(walk, walk)} walk: q = A p with the p.q partial, FP64)"),
             "bytes_per_launch": mv_bytes, "format_bytes_per_launch": fmt_bytes,
             # the same launches counted in the bytes of the format the walk

@@ -52,8 +52,10 @@ __device__ __forceinline__ int32_t wg_max(int32_t v, int32_t* red) {
 // found one after the other, each the first row's that has none yet, and
 // compared with every such row's in LDS.  A mesh tile has 1 to about 12; a
 // tile whose first kPatTry lists hold less than a quarter of its rows is
-// given up.  *nopat is set where a tile has no patterns, and no further tile
-// looks for any.
+// given up.  *nopat is set where a tile with a window has no patterns, and no
+// further tile looks for any; one without a window shows in stats[0] (a store
+// to one address by each of them took 1.2 ms instead of 0.24 on 5M rows of
+// random columns).
 __global__ __launch_bounds__(kWinRows) void k_win_tiles(int64_t n, const int32_t* __restrict__ rowptr,
                                                         const int32_t* __restrict__ col,
                                                         const uint32_t* __restrict__ off,
@@ -131,10 +133,7 @@ __global__ __launch_bounds__(kWinRows) void k_win_tiles(int64_t n, const int32_t
              __hip_atomic_load(&stats[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
       atomicMax(&stats[1], (unsigned long long)c);
   }
-  if (c == 0) {
-    if (tid == 0) *nopat = 1;
-    return;
-  }
+  if (c == 0) return;
   const int32_t rs = tid < r1 - r0 ? rowptr[r0 + tid] - t0 : 0;
   const int32_t len = tid < r1 - r0 ? rowptr[r0 + tid + 1] - t0 - rs : 0;
   const bool fit = __syncthreads_and(len <= kPatLen);
@@ -152,7 +151,9 @@ __global__ __launch_bounds__(kWinRows) void k_win_tiles(int64_t n, const int32_t
     if (fit) lc[e - t0] = v;
   }
   __shared__ uint32_t quit;
-  if (tid == 0) quit = __hip_atomic_load(nopat, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (tid == 0)
+    quit = __hip_atomic_load(nopat, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) |
+           (__hip_atomic_load(&stats[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0);
   __syncthreads();
   if (quit) return;
   int id = len > 0 ? -1 : 0;
@@ -263,7 +264,7 @@ void window_keep(Csr& A, const uint32_t* stats, Window* w) {
     A.win.max_blocks = largest;
     A.win.total_blocks = total;
     A.win.gather_entries = gather;
-    A.win.patterned = stats[5] == 0;
+    A.win.patterned = stats[5] == 0 && gather == 0;
     *w = Window();
   } else {
     window_release(w);
