@@ -157,14 +157,41 @@ __global__ void k_seg_lengths(const uint32_t* __restrict__ order, const uint32_t
   len[e] = start[r + 1] - a;
 }
 
+// The first run from e on, up to lim, that is not of run e - 1's row.  Galloped
+// for: most rows end within a few runs, and one step after the other was a
+// chain of 1024 loads for rows that exceed a tile (158 us).
+__device__ __forceinline__ int64_t row_end(const uint32_t* __restrict__ row, int64_t e,
+                                           int64_t lim) {
+  if (e == 0 || e >= lim) return e < lim ? e : lim;
+  const uint32_t r = row[e - 1];
+  if (row[e] != r) return e;
+  int64_t step = 1;  // row[e] is r
+  while (e + step < lim && row[e + step] == r) {
+    e += step;
+    step *= 2;
+  }
+  int64_t hi = e + step < lim ? e + step : lim;  // another row, or the limit
+  while (hi - e > 1) {
+    const int64_t mid = e + (hi - e) / 2;
+    if (row[mid] == r)
+      e = mid;
+    else
+      hi = mid;
+  }
+  return hi;
+}
+
 // tile[b] = the first run that starts a row and whose first item is at b
 // kRowTile or later, for b = 0 .. tiles (row: the runs' rows in order; SEG:
 // pos their first items, pos[count] the item count; else every item is a
-// run), with that run's first item.  The search stops kRowCap + 1 runs on: the rows of the tile before
-// then exceed a tile's capacity, wherever the next row starts.
+// run), with that run's first item.  The search stops kRowCap + 1 runs on: the
+// rows of the tile before then exceed a tile's capacity, wherever the next
+// row starts.  *longrow is set where the items passed over do already, which
+// spares the stage that follows its work for nothing.
 template <bool SEG>
 __global__ void k_row_tiles(const uint32_t* __restrict__ row, const uint32_t* __restrict__ pos,
-                            int64_t count, int64_t tiles, uint2* __restrict__ tile) {
+                            int64_t count, int64_t tiles, uint2* __restrict__ tile,
+                            uint32_t* __restrict__ longrow) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   int64_t lo, hi, e = t;
   uint64_t heads = 0;
@@ -186,9 +213,11 @@ __global__ void k_row_tiles(const uint32_t* __restrict__ row, const uint32_t* __
     const uint64_t m = heads >> lane;
     e += m ? __ffsll((unsigned long long)m) - 1 : 64 - lane;
   }
-  while (e > 0 && e < lim && row[e] == row[e - 1]) ++e;
-  if (e > lim) e = lim;
+  const int64_t from = SEG ? t : e;
+  e = row_end(row, e, lim);
   const uint2 v = make_uint2((uint32_t)e, SEG ? pos[e] : (uint32_t)e);
+  // (runs from .. e are one row's, the row of run from - 1)
+  if (e > from && v.y - (SEG ? pos[from] : (uint32_t)from) > (uint32_t)kRowCap) *longrow = 1;
   for (int64_t b = lo; b <= hi; ++b) tile[b] = v;
 }
 
@@ -272,6 +301,7 @@ struct RowTiles {
   uint32_t* rent;
   uint32_t* rtile;
   int32_t* rdiag;
+  const uint32_t* longrow;  // a tile will overflow
   uint32_t* overflow;
 };
 
@@ -301,8 +331,14 @@ __global__ __launch_bounds__(kBlock) void k_rowtile_sort(RowTiles t) {
   const int64_t b = blockIdx.x;
   const uint2 ta = t.tile[b], tb = t.tile[b + 1];
   const int64_t s0 = ta.x, s1 = tb.x, q0 = ta.y, items = (int64_t)tb.y - q0;
-  if (s0 >= s1) {  // no row starts here
-    if (tid == 0) t.ecount[b] = 0;
+  // no row starts here, or nothing will be built (longrow was set before this
+  // kernel, so it is the same for every thread)
+  const bool none = *t.longrow != 0;
+  if (s0 >= s1 || none) {
+    if (tid == 0) {
+      t.ecount[b] = 0;
+      if (none) atomicOr(t.overflow, 1u);
+    }
     return;
   }
   if (s1 - s0 > kRowCap || items > kRowCap) {
@@ -806,9 +842,20 @@ struct Parts {
 
 // The counts' words in misc: an index out of range, kept triplets, kept
 // triplets and runs of equal rows together, a row tile that overflowed,
-// entries, the row statistics, the window index's statistics.
-enum { kErr = 0, kKept = 1, kBoth = 2, kOver = 3, kNnz = 4, kStats = 5, kWin = 10, kMisc = 16 };
-static_assert(kWin % 2 == 0 && kWin + kWinStats <= kMisc, "misc holds the statistics");
+// entries, the row statistics, the window index's statistics, a row found to
+// exceed a tile beforehand.
+enum {
+  kErr = 0,
+  kKept = 1,
+  kBoth = 2,
+  kOver = 3,
+  kNnz = 4,
+  kStats = 5,
+  kWin = 10,
+  kLong = 16,
+  kMisc = 18
+};
+static_assert(kWin % 2 == 0 && kWin + kWinStats <= kLong, "misc holds the statistics");
 
 struct CooIn {
   const int32_t* i;
@@ -912,6 +959,7 @@ int symbolic_rows(spx_matrix* h, const CooIn& in, hipStream_t s, bool* overflow)
   t.rtile = w + o_rtile;
   t.rdiag = (int32_t*)(w + o_rdiag);
   t.overflow = in.misc + kOver;
+  t.longrow = in.misc + kLong;
   uint2* tile = reinterpret_cast<uint2*>(w + o_tile);
   t.tile = tile;
   hipLaunchKernelGGL(k_row_init, dim3(grid_for(n, 256)), dim3(256), 0, s, t.rent, t.rtile, t.rdiag,
@@ -926,7 +974,7 @@ int symbolic_rows(spx_matrix* h, const CooIn& in, hipStream_t s, bool* overflow)
                        w + o_start, count, w + o_first, w + o_pos);
     SPX_TRY(exclusive_scan_u32(w + o_pos, w + o_pos, count, w + o_pos + count, work, s));
     hipLaunchKernelGGL(k_row_tiles<true>, dim3(grid_for(count + 1, 256)), dim3(256), 0, s, row,
-                       w + o_pos, count, tiles, tile);
+                       w + o_pos, count, tiles, tile, in.misc + kLong);
     t.row = row;
     t.first = w + o_first;
     t.pos = w + o_pos;
@@ -942,7 +990,7 @@ int symbolic_rows(spx_matrix* h, const CooIn& in, hipStream_t s, bool* overflow)
                                  all_kept ? reinterpret_cast<const uint32_t*>(in.i) : nullptr,
                                  all_kept));
     hipLaunchKernelGGL(k_row_tiles<false>, dim3(grid_for(tiles + 1, 256)), dim3(256), 0, s, row,
-                       (const uint32_t*)nullptr, count, tiles, tile);
+                       (const uint32_t*)nullptr, count, tiles, tile, in.misc + kLong);
     t.row = row;
     t.first = order;
     hipLaunchKernelGGL(k_rowtile_sort<false>, dim3((unsigned)tiles), dim3(kBlock), 0, s, t);
@@ -1044,7 +1092,8 @@ int symbolic(spx_matrix* h, const int32_t* i, const int32_t* j, hipStream_t s) {
                      (long long)n);
   const CooIn in{i, j, ntiles, host[kKept], (int64_t)host[kBoth] - host[kKept], misc, cnt};
   h->nvalid = in.nvalid;
-  if (h->colbits <= kRowColBits) {
+  // (with more triplets than all rows' tiles hold, one of them overflows)
+  if (h->colbits <= kRowColBits && in.nvalid <= kRowCap * n) {
     bool overflow = false;
     SPX_TRY(symbolic_rows(h, in, s, &overflow));
     if (!overflow) return SPX_OK;

@@ -51,3 +51,40 @@ def test_overflowed_vector_many_rows_bitwise(orc):
     got = dev(x)
     V.set_values_coo(dev(prob.v), got, mode=spx.ADD_VALUES)
     assert np.array_equal(bits(host(got)), bits(orc.vec_coo(prob.n, prob.i, prob.v, x, mode=1)))
+
+
+@pytest.mark.parametrize("run", [1, 7])
+@pytest.mark.parametrize("longest", [1023, 1024, 1025, 1535, 1537, 2600, 300000])
+def test_long_row_at_every_place_bitwise(orc, longest, run):
+    """One row of about a tile's capacity, or far above, after 0 to 600 other
+    triplets (the tile boundary falls at its start, inside and at its end)."""
+    spx = require_gpu()
+    rng = np.random.default_rng(longest)
+    for before in (0, 1, 511, 512, 600):
+        rows = np.concatenate([np.arange(before) // 3, np.full(longest // run, 300),
+                               301 + np.arange(700) // 2])
+        i = np.repeat(rows, run)
+        prob = W.CooProblem(n=2000, i=i.astype(np.int32),
+                            j=rng.integers(0, 2000, i.size).astype(np.int32),
+                            v=rng.uniform(-1, 1, i.size))
+        A = spx.coo_preallocate(prob.n, dev(prob.i), dev(prob.j))
+        A.set_values_coo(dev(prob.v))
+        ref = orc.assemble(prob.n, prob.i, prob.j, prob.v)
+        csr_equal(ref, *(host(t) for t in A.get_csr()))
+        assert np.array_equal(host(A.get_coo_maps()[1]), ref.perm)
+
+
+@pytest.mark.parametrize("n", [1, 3, 500])
+def test_rows_as_full_as_tiles_bitwise(orc, n):
+    """Exactly as many triplets as the rows' tiles hold, and one more."""
+    spx = require_gpu()
+    rng = np.random.default_rng(n)
+    for extra in (0, 1):
+        i = np.concatenate([np.repeat(np.arange(n), 1024), np.full(extra, n // 2)])
+        prob = W.CooProblem(n=n, i=i.astype(np.int32),
+                            j=rng.integers(0, n, i.size).astype(np.int32),
+                            v=rng.uniform(-1, 1, i.size))
+        A = spx.coo_preallocate(n, dev(prob.i), dev(prob.j))
+        A.set_values_coo(dev(prob.v))
+        ref = orc.assemble(n, prob.i, prob.j, prob.v)
+        csr_equal(ref, *(host(t) for t in A.get_csr()))
