@@ -337,7 +337,7 @@ __global__ __launch_bounds__(kBlock) void k_rowtile_sort(RowTiles t) {
   if (s0 >= s1 || none) {
     if (tid == 0) {
       t.ecount[b] = 0;
-      if (none) atomicOr(t.overflow, 1u);
+      if (none && b == 0) atomicOr(t.overflow, 1u);  // (one for all: they take turns)
     }
     return;
   }
