@@ -835,7 +835,7 @@ size_t shape_lds(const SpmvShape& sh) {
 // 9.8.
 constexpr int64_t kPatternTilesPerCu = 2;
 bool use_pattern(const spx_matrix* h, const SpmvShape& sh, const Csr& M) {
-  if (!M.win.patterned || !sh.nt || h->fused_opt > 0 || h->xcd_remap > 0) return false;
+  if (!rows_repeat_enough(M) || !sh.nt || h->fused_opt > 0 || h->xcd_remap > 0) return false;
   if (sh.variant == kVariantWindow) return true;
   return h->variant_opt == kVariantAuto && !h->rows_opt && !h->rows32_opt && !h->vec_opt &&
          !h->pipe_opt && !h->lanes_opt && ceil_div(M.n, kWinRows) >= kPatternTilesPerCu * cu_count();

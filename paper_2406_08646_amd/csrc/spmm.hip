@@ -737,16 +737,26 @@ int build_rowset(Csr& A, int rows, hipStream_t s) {
 
 // The pattern product where it is the fastest; *launched is false elsewhere.
 // By entries a row (steps) and the figures above: every width up to 32 but 16
-// on long rows (16 columns by row sets, below: 160 us, 204 by this), up to 24
-// there where the windows leave panels of 6 columns (111^3 rows: 24 columns
-// 641 and 552, 32 columns 657 and 787); up to 6 on rows of about 9 entries;
-// on shorter ones up to 4, and 6 from ten tiles per CU (1001^2 rows 52 and
-// 46, 501^2 13.6 and 15.1); up to 8 on short rows where X or Y is not 16-byte
-// aligned or has odd strides, as with odd numbers of columns (the gathering
-// kernels then load 8 bytes at a time: 5 columns on 501^2 rows 20.5 and
-// 14.7).  From one tile per CU (41^3 rows: 2 columns 20 and 9.5, 12 columns
+// on long rows (16 columns by row sets, below: 160 us, 204 by this), up to 12
+// there where the windows leave panels of 6 columns, since each panel reads
+// its part of the lines of X again and the windows of the tiles in flight
+// outgrow L2 (130^3 rows: 12 columns 558 and 439, 14 columns 567 and 712, 24
+// columns 984 and 1439; 165^3 1151 and 1061, 1174 and 1749, 2090 and 3262;
+// 127^3 516 and 362, 525 and 525, 916 and 943); up to 6 on rows of about 9
+// entries; on shorter ones up to 4, and 6 from ten tiles per CU (1001^2 rows
+// 52 and 46, 501^2 13.6 and 15.1); up to 8 on short rows where X or Y is not
+// 16-byte aligned or has odd strides, as with odd numbers of columns (the
+// gathering kernels then load 8 bytes at a time: 5 columns on 501^2 rows 20.5
+// and 14.7).  From one tile per CU (41^3 rows: 2 columns 20 and 9.5, 12 columns
 // 24 and 21; below they are alike); more than 16 columns from four (64^3: 24
-// columns 113 and 70; 41^3: 32 columns 39 and 47).
+// columns 113 and 70; 41^3: 32 columns 39 and 47).  Rows of few entries
+// load too little of X for its staging to pay: one or two columns from 2
+// entries a row (2 columns, 10^6 rows of 1 entry 13.0 and 14.5, of 2 18.1 and
+// 14.9), up to 4, or not 16-byte aligned, from 3 (4 columns, 10^6 rows of 2
+// entries 20 and 26, of 3 27.6 and 27.3; 7 columns of 2 50 and 55, of 3 65
+// and 57), and from 5 for the other widths and below ten tiles per CU (6
+// columns, 10^6 rows of 4 entries 40.5 and 44.2, of 5 51 and 45; 3 columns,
+// 3 x 10^5 rows of 4 12.7 and 13.3, of 5 15.5 and 13.4).
 int launch_spmm_pattern(const Csr& A, int64_t nrhs, const double* X, int64_t ldx, double* Y,
                         int64_t ldy, hipStream_t s, bool* launched) {
   *launched = false;
@@ -755,8 +765,11 @@ int launch_spmm_pattern(const Csr& A, int64_t nrhs, const double* X, int64_t ldx
   const bool a16 = ((reinterpret_cast<uintptr_t>(X) | reinterpret_cast<uintptr_t>(Y)) & 15) == 0 &&
                    ldx % 2 == 0 && ldy % 2 == 0;
   const bool many = tiles >= 10 * (int64_t)cu_count();
-  const int64_t widest = steps > 5 ? (blocks <= 24 ? 32 : 24) : !a16 ? 8 : steps > 3 || many ? 6 : 4;
-  if (!A.win.patterned || nrhs == 0 || nrhs == 16 || nrhs > widest || ldx > (1 << 20) ||
+  const int64_t widest = steps > 5 ? (blocks <= 24 ? 32 : 12) : !a16 ? 8 : steps > 3 || many ? 6 : 4;
+  // twice the fewest entries a row
+  const int64_t fewest = nrhs <= 2 ? 3 : many && (nrhs <= 4 || !a16) ? 5 : 9;
+  if (!A.win.patterned || 2 * A.nnz <= fewest * A.n || nrhs == 0 || nrhs == 16 ||
+      nrhs > widest || ldx > (1 << 20) ||
       tiles < (nrhs > 16 ? 4 : 1) * (int64_t)cu_count())
     return SPX_OK;
   auto go = [&](auto f) -> int {

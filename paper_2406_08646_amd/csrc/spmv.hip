@@ -618,9 +618,20 @@ SpmvShape solver_shape(const spx_matrix* h, const Csr& A) {
   return sh;
 }
 
+// The pattern walk has no other loads and order.  On rows of up to about 10
+// entries it reads nearly as many bytes as the window walk and falls behind it
+// on the largest systems, where a workgroup's tiles lie far apart.  us a
+// product by the window walk and by it: 5 points, 2000^2 rows 50.7 and 47.0,
+// 2500^2 83 and 87, 4000^2 198 and 222; 9 points, 2500^2 117 and 115, 4000^2
+// 311 and 320; 7 points, 160^3 rows 69 and 67, 200^3 131 and 135.
+constexpr int64_t kPatternTilesPerCu3 = 80, kPatternTilesPerCu5 = 100;
 bool walks_patterns(const Csr& A, const SpmvShape& sh, int remap) {
-  // the pattern walk has no other loads and order
-  if (sh.variant != kVariantWindow || !sh.nt || remap) return false;
+  if (sh.variant != kVariantWindow || !sh.nt || remap || !rows_repeat_enough(A)) return false;
+  const int64_t steps = ceil_div(A.tile_nnz[3] + 1, kWinRows * 2);
+  const int64_t most = steps <= 3   ? kPatternTilesPerCu3
+                       : steps <= 5 ? kPatternTilesPerCu5
+                                    : INT32_MAX;
+  if (ceil_div(A.n, kWinRows) > most * cu_count()) return false;
   bool form = false;
   (void)with_pattern<double>(A, [&](auto) {
     form = true;

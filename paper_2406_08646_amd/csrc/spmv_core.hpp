@@ -735,7 +735,18 @@ unsigned pattern_blocks(int64_t tiles, int64_t limit = INT32_MAX) {
 // with 4, 96 with 5 (spilling), 5 steps 78 with 4 and 79 with 5; 14 steps
 // need 70 KB of LDS and take 2; fp32, ms a solve: 7 steps 17.8 with 4, 17.4
 // with 3 and 17.3 with 5 on 96^3 rows, 37.8, 37.7 and 39.8 on 128^3; 3 steps
-// 383 with 6, 386 with 5, 493 with 8.
+// 383 with 6, 386 with 5, 493 with 8.  In fp64 short rows with windows past 20
+// blocks have none: 7 points, 252^3 rows (22 blocks) take 342 us by the
+// 14-step form and 257 by the window walk, the solvers' first kernel 357 and
+// 324 (and 183 in fp32, 207).
+//
+// rows_repeat_enough: rows long enough for that, whatever the size.  Up to 3
+// entries the lists take as many bytes as 16-bit columns: 3 entries, 10^6 rows
+// 12.6 us a product and 11.1 by the window walk, the solvers' first kernel
+// 16.8 and 16.0 (in fp32 13.7 and 14.6); 1 entry, 4 x 10^6 rows 38 and 32, 49
+// and 38 (35 and 38); 4 entries 15.6 and 15.7.
+inline bool rows_repeat_enough(const Csr& A) { return A.win.patterned && 2 * A.nnz > 7 * A.n; }
+
 template <typename VT, typename F>
 int with_pattern(const Csr& A, F&& f) {
   if (!A.win.patterned) return SPX_OK;
@@ -744,8 +755,8 @@ int with_pattern(const Csr& A, F&& f) {
   if constexpr (sizeof(VT) == 8) {
     if (steps <= 3 && blocks <= 20) return f(Pattern<3, 5, 4, 4>());
     if (steps <= 5 && blocks <= 20) return f(Pattern<5, 5, 4, 4>());
-    if (steps <= 14 && blocks <= 24) return f(Pattern<14, 6, 2, 16>());
-    if (steps <= 14 && blocks <= 32) return f(Pattern<14, 8, 2, 16>());
+    if (steps > 5 && steps <= 14 && blocks <= 24) return f(Pattern<14, 6, 2, 16>());
+    if (steps > 5 && steps <= 14 && blocks <= 32) return f(Pattern<14, 8, 2, 16>());
   } else {
     if (steps <= 3 && blocks <= 20) return f(Pattern<3, 5, 6, 8>());
     if (steps <= 7 && blocks <= 24) return f(Pattern<7, 6, 4, 8>());

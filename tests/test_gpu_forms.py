@@ -16,11 +16,11 @@ pytestmark = pytest.mark.gpu
 LAUNCHES, ONE_WORKGROUP, HELD, COOPERATIVE = 1, 2, 3, 4
 
 
-# rows past 32 entries; more than 16 lists in a tile (lists15 and 16 and the
-# long rows with those that the matrix's edge cuts off); windows past 32
-# blocks; an index that does not pay
-WITHOUT = {"length27", "length28", "length32", "length33", "lists15", "lists16", "lists17",
-           "lists40", "groups7", "groups8", "row1"}
+# rows of up to 3 entries on average; rows past 32 entries; more than 16 lists
+# in a tile (lists15 and 16 and the long rows with those that the matrix's edge
+# cuts off); windows past 32 blocks; an index that does not pay
+WITHOUT = {"length1", "length2", "empty_rows", "empty_tile", "length27", "length28", "length32",
+           "length33", "lists15", "lists16", "lists17", "lists40", "groups7", "groups8", "row1"}
 
 
 @pytest.mark.parametrize("case", sorted(CASES))
@@ -41,7 +41,7 @@ def test_products_by_row_patterns(case):
 def whole_lists(n, lists, seed):
     """Row r has the columns base(r) + lists[r % len(lists)], all of them in
     range, so every tile has exactly those lists."""
-    width = 1 + max(max(o) for o in lists)
+    width = 1 + max(max(o, default=0) for o in lists)
     base = np.clip(np.arange(n) - width // 2, 0, n - width)
     i = np.concatenate([np.full(len(lists[r % len(lists)]), r) for r in range(n)])
     j = np.concatenate([base[r] + np.asarray(lists[r % len(lists)]) for r in range(n)])
@@ -52,9 +52,14 @@ def whole_lists(n, lists, seed):
 LIMITS = {  # the longest lists, the fullest tiles (7167 entries) and the most lists, and past each
     "full27": ([range(27)], 1), "full28": ([range(28)], 0),
     "mixed32": ([range(32), range(23)], 1), "mixed33": ([range(33), range(22)], 0),
-    "lists15": ([[0, 1, 2 + k] for k in range(15)], 1),
-    "lists16": ([[0, 1, 2 + k] for k in range(16)], 1),
-    "lists17": ([[0, 1, 2 + k] for k in range(17)], 0)}
+    "lists15": ([[0, 1, 2, 3 + k] for k in range(15)], 1),
+    "lists16": ([[0, 1, 2, 3 + k] for k in range(16)], 1),
+    "lists17": ([[0, 1, 2, 3 + k] for k in range(17)], 0),
+    # rows of 3 and of 4 entries on average; empty and single-entry rows among
+    # longer ones; whole tiles of empty rows
+    "short3": ([range(3)], 0), "short4": ([range(4)], 1), "short3and4": ([range(3), range(4)], 0),
+    "empty_rows": ([[], range(9), [2]] + 2 * [range(4)], 1),
+    "empty_tile": ([[]] * 600 + [range(11)] * 500, 1)}
 
 
 @pytest.mark.parametrize("case", sorted(LIMITS))
