@@ -14,8 +14,9 @@
 // (nontemporal: 7.0 TB/s against 6.2 for a plain sweep of 4 GB) and no load
 // waits for another.  Stores among the loads cost far more than their bytes
 // (80 MB stored during a 4 GB sweep take 120 us, where a copy of as much
-// takes 35), so a new pair is stored by a kernel of its own and a pass
-// holds its results in LDS and stores many at once.
+// takes 35), so a new pair is stored by a kernel of its own (by the pass
+// where the history is short) and a pass holds its results in LDS and stores
+// many at once.
 // n = 10^7, m = 50, one update and apply: 2685 us with S and Y as whole
 // columns, 80 MB apart (S^T y and S^T g 894, a and Y^T a 918, p 789, the two
 // solves 14 each, at 4.4-5.1 TB/s), 2180 so (728, 716, 658, 17 and 11; 592
@@ -56,6 +57,12 @@ namespace spx {
 namespace {
 
 constexpr int kMaxHistory = 64;
+// Up to this many pairs the pass over S stores the new one (us an update by a
+// kernel of its own and so: n = 10^7, m = 3 108 and 94, m = 4 129 and 109; n =
+// 1000 10 and 7.5), above it, more streams among the stores, that takes
+// longer (a step at m = 6, n = 10^7 427 and 439, at m = 5, n = 5 x 10^5 38.1
+// and 39.1; m = 50 below).
+constexpr int kPutInPass = 4;
 constexpr int kLB = 256;
 constexpr int kWaves = kLB / 64;
 constexpr int kTileRows = 128;  // two rows per lane, 16-byte loads
@@ -108,10 +115,12 @@ __device__ __forceinline__ dbl2 load_once(const double* p) {
 template <int NC>
 struct Cols {
   int lo, nc;
+  int newest;  // place of the newest pair's column, or -1
   int off[NC];
   __device__ __forceinline__ Cols(const Ring& R, int w) {
     lo = R.cnt * w / kWaves;
     nc = R.cnt * (w + 1) / kWaves - lo;
+    newest = lo + nc == R.cnt && nc > 0 ? nc - 1 : -1;
 #pragma unroll
     for (int u = 0; u < NC; ++u) off[u] = R.slot(lo + u) * kTileRows;
   }
@@ -150,10 +159,12 @@ __global__ __launch_bounds__(kLB) void k_lb_put(int64_t n, int64_t tiles, int m,
 // takes a quarter of the columns of every tile, all of a step's loads in
 // flight together, so every element of the history is read once and w1 and
 // w2 once per workgroup.  Every column's products are added in the same
-// order with and without BOTH.
-template <int NC, bool BOTH>
-__global__ __launch_bounds__(kLB) void k_lb_dots(int64_t n, int64_t tiles,
-                                                 const double* __restrict__ S, Ring R,
+// order with and without BOTH.  PUT: the newest pair is (s, w1) and not yet
+// stored; the wave that has its column takes it from s and stores both.
+template <int NC, bool BOTH, bool PUT>
+__global__ __launch_bounds__(kLB) void k_lb_dots(int64_t n, int64_t tiles, double* __restrict__ S,
+                                                 double* __restrict__ Y, Ring R,
+                                                 const double* __restrict__ s,
                                                  const double* __restrict__ w1,
                                                  const double* __restrict__ w2,
                                                  double* __restrict__ P, int row1, int row2) {
@@ -171,7 +182,23 @@ __global__ __launch_bounds__(kLB) void k_lb_dots(int64_t n, int64_t tiles,
     dbl2 v2 = {0.0, 0.0};
     if constexpr (BOTH) v2 = load2(w2, r, n);
     dbl2 c[NC];
-    C.load(c, S + t * R.m * kTileRows + 2 * lane);
+    const int64_t o = t * R.m * kTileRows + 2 * lane;
+    if constexpr (PUT) {
+      dbl2 sv = {0.0, 0.0};
+      if (C.newest >= 0) sv = load2(s, r, n);
+#pragma unroll
+      for (int u = 0; u < NC; ++u) {
+        c[u] = dbl2{0.0, 0.0};
+        if (C.has(u) && u != C.newest) c[u] = load_once(S + o + C.off[u]);
+        if (u == C.newest) {
+          c[u] = sv;
+          *reinterpret_cast<dbl2*>(S + o + C.off[u]) = sv;
+          *reinterpret_cast<dbl2*>(Y + o + C.off[u]) = v;
+        }
+      }
+    } else {
+      C.load(c, S + o);
+    }
 #pragma unroll
     for (int u = 0; u < NC; ++u) {
       acc[u] += c[u].x * v.x;
@@ -263,6 +290,107 @@ __global__ __launch_bounds__(kLB) void k_lb_ya(int64_t n, int64_t tiles,
       if (lane == 0) P[(int64_t)(C.lo + u) * gridDim.x + blockIdx.x] = d;
     }
   }
+}
+
+// --------------------------------------------------- one or two columns
+// The same two passes where a quarter of the columns would leave waves
+// without any: a wave per tile with all NC = cnt columns, which keeps four
+// times as many bytes in flight and needs no exchange between waves.  NC = 1,
+// n = 10^7, a step of 228 us with whole columns, 247 with those waves idle,
+// 182 so (NC = 2 301, 270 and 226).
+template <int NC>
+__device__ __forceinline__ void few_partials(double (&v)[NC], double* __restrict__ P, int row) {
+  __shared__ double part[NC][kWaves];
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+#pragma unroll
+  for (int u = 0; u < NC; ++u) {
+    const double d = wave_sum(v[u]);
+    if (lane == 0) part[u][w] = d;
+  }
+  __syncthreads();
+  if (threadIdx.x < NC) {
+    double d = 0.0;
+#pragma unroll
+    for (int q = 0; q < kWaves; ++q) d += part[threadIdx.x][q];
+    P[(int64_t)(row + threadIdx.x) * gridDim.x + blockIdx.x] = d;
+  }
+  __syncthreads();
+}
+
+template <int NC, bool BOTH, bool PUT>
+__global__ __launch_bounds__(kLB) void k_lb_few_dots(int64_t n, int64_t tiles,
+                                                     double* __restrict__ S, double* __restrict__ Y,
+                                                     Ring R, const double* __restrict__ s,
+                                                     const double* __restrict__ w1,
+                                                     const double* __restrict__ w2,
+                                                     double* __restrict__ P, int row1, int row2) {
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  double acc[NC] = {}, acc2[NC] = {};
+  for (int64_t t = (int64_t)blockIdx.x * kWaves + w; t < tiles; t += (int64_t)gridDim.x * kWaves) {
+    const int64_t r = t * kTileRows + 2 * lane;
+    const dbl2 v = load2(w1, r, n);
+    dbl2 v2 = {0.0, 0.0}, c[NC];
+    if constexpr (BOTH) v2 = load2(w2, r, n);
+    const int64_t o = t * R.m * kTileRows + 2 * lane;
+#pragma unroll
+    for (int u = 0; u < NC; ++u) {
+      if (PUT && u == NC - 1)
+        c[u] = load2(s, r, n);
+      else
+        c[u] = load_once(S + o + R.slot(u) * kTileRows);
+    }
+    if constexpr (PUT) {
+      *reinterpret_cast<dbl2*>(S + o + R.slot(NC - 1) * kTileRows) = c[NC - 1];
+      *reinterpret_cast<dbl2*>(Y + o + R.slot(NC - 1) * kTileRows) = v;
+    }
+#pragma unroll
+    for (int u = 0; u < NC; ++u) {
+      acc[u] += c[u].x * v.x;
+      acc[u] += c[u].y * v.y;
+      if constexpr (BOTH) {
+        acc2[u] += c[u].x * v2.x;
+        acc2[u] += c[u].y * v2.y;
+      }
+    }
+  }
+  few_partials<NC>(acc, P, row1);
+  if constexpr (BOTH) few_partials<NC>(acc2, P, row2);
+}
+
+template <int NC, bool H0>
+__global__ __launch_bounds__(kLB) void k_lb_few_ya(int64_t n, int64_t tiles,
+                                                   const double* __restrict__ Y, Ring R,
+                                                   const double* __restrict__ g,
+                                                   const double* __restrict__ h0,
+                                                   const double* __restrict__ red,
+                                                   double* __restrict__ a_out,
+                                                   double* __restrict__ P) {
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  double f[NC] = {}, c[NC];
+#pragma unroll
+  for (int u = 0; u < NC; ++u) c[u] = red[u];
+  for (int64_t t = (int64_t)blockIdx.x * kWaves + w; t < tiles; t += (int64_t)gridDim.x * kWaves) {
+    const int64_t r = t * kTileRows + 2 * lane;
+    const dbl2 gv = load2(g, r, n);
+    dbl2 hv = {1.0, 1.0}, y[NC];
+    if constexpr (H0) hv = load2(h0, r, n);
+#pragma unroll
+    for (int u = 0; u < NC; ++u)
+      y[u] = load_once(Y + t * R.m * kTileRows + 2 * lane + R.slot(u) * kTileRows);
+    dbl2 a = {0.0, 0.0};
+#pragma unroll
+    for (int u = 0; u < NC; ++u) a += y[u] * c[u];
+    a = gv + a;
+    if constexpr (H0) a = hv * a;
+    a = dbl2{r < n ? a.x : 0.0, r + 1 < n ? a.y : 0.0};
+    *reinterpret_cast<dbl2*>(a_out + t * kTileRows + 2 * lane) = a;
+#pragma unroll
+    for (int u = 0; u < NC; ++u) {
+      f[u] += y[u].x * a.x;
+      f[u] += y[u].y * a.y;
+    }
+  }
+  few_partials<NC>(f, P, 0);
 }
 
 // ------------------------------------------------------------ p = a - S e
@@ -498,26 +626,37 @@ int apply_passes(spx_lbfgs* h, const double* g, const double* h0, double* p, hip
   const int64_t n = h->n;
   const unsigned G = blocks(h, h->count);
   const Ring R{h->m, h->start, h->count};
+  const double* none = nullptr;
   if (have_q) {
     hipLaunchKernelGGL((k_lb_solve<true, 1>), dim3(1), dim3(kSolve), 0, st, h->P, (int64_t)G, R,
                        2 * kMaxHistory, h->SY, h->red);
   } else {
-    with_cols(R.cnt, [&](auto nc) {
-      hipLaunchKernelGGL((k_lb_dots<decltype(nc)::value, false>), dim3(G), dim3(kLB), 0, st, n,
-                         h->tiles, h->S, R, g, (const double*)nullptr, h->P, 0, 0);
-    });
+    auto dots = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(G), dim3(kLB), 0, st, n, h->tiles, h->S, h->Y, R, none, g, none,
+                         h->P, 0, 0);
+    };
+    if (R.cnt == 1)
+      dots(k_lb_few_dots<1, false, false>);
+    else if (R.cnt == 2)
+      dots(k_lb_few_dots<2, false, false>);
+    else
+      with_cols(R.cnt, [&](auto nc) { dots(k_lb_dots<decltype(nc)::value, false, false>); });
     hipLaunchKernelGGL((k_lb_solve<false, 1>), dim3(1), dim3(kSolve), 0, st, h->P, (int64_t)G, R, 0,
                        h->SY, h->red);
   }
-  with_cols(R.cnt, [&](auto nc) {
-    constexpr int NC = decltype(nc)::value;
-    if (h0)
-      hipLaunchKernelGGL((k_lb_ya<NC, true>), dim3(G), dim3(kLB), 0, st, n, h->tiles, h->Y, R, g, h0,
-                         h->red, h->a, h->P);
-    else
-      hipLaunchKernelGGL((k_lb_ya<NC, false>), dim3(G), dim3(kLB), 0, st, n, h->tiles, h->Y, R, g,
-                         h0, h->red, h->a, h->P);
-  });
+  auto ya = [&](auto with_h0, auto without) {
+    hipLaunchKernelGGL(h0 ? with_h0 : without, dim3(G), dim3(kLB), 0, st, n, h->tiles, h->Y, R, g, h0,
+                       h->red, h->a, h->P);
+  };
+  if (R.cnt == 1)
+    ya(k_lb_few_ya<1, true>, k_lb_few_ya<1, false>);
+  else if (R.cnt == 2)
+    ya(k_lb_few_ya<2, true>, k_lb_few_ya<2, false>);
+  else
+    with_cols(R.cnt, [&](auto nc) {
+      constexpr int NC = decltype(nc)::value;
+      ya(k_lb_ya<NC, true>, k_lb_ya<NC, false>);
+    });
   hipLaunchKernelGGL((k_lb_solve<false, 2>), dim3(1), dim3(kSolve), 0, st, h->P, (int64_t)G, R, 0,
                      h->SY, h->red);
   with_cols(R.cnt, [&](auto nc) {
@@ -606,17 +745,36 @@ int update_impl(spx_lbfgs* h, const double* s, const double* y, const double* g,
   }
   const unsigned G = blocks(h, cnt);
   const Ring R{h->m, start, cnt};
-  hipLaunchKernelGGL(k_lb_put, dim3((unsigned)ceil_div(h->tiles, kWaves)), dim3(kLB), 0, st, h->n,
-                     h->tiles, h->m, slot, s, y, h->S, h->Y);
-  with_cols(cnt, [&](auto nc) {
-    constexpr int NC = decltype(nc)::value;
-    if (g)
-      hipLaunchKernelGGL((k_lb_dots<NC, true>), dim3(G), dim3(kLB), 0, st, h->n, h->tiles, h->S, R, y,
-                         g, h->P, kMaxHistory, 2 * kMaxHistory);
+  const bool put = cnt > kPutInPass;
+  if (put)
+    hipLaunchKernelGGL(k_lb_put, dim3((unsigned)ceil_div(h->tiles, kWaves)), dim3(kLB), 0, st, h->n,
+                       h->tiles, h->m, slot, s, y, h->S, h->Y);
+  auto dots = [&](auto kernel, int row2) {
+    hipLaunchKernelGGL(kernel, dim3(G), dim3(kLB), 0, st, h->n, h->tiles, h->S, h->Y, R, s, y, g, h->P,
+                       kMaxHistory, row2);
+  };
+  if (put) {
+    with_cols(cnt, [&](auto nc) {
+      constexpr int NC = decltype(nc)::value;
+      if (g)
+        dots(k_lb_dots<NC, true, false>, 2 * kMaxHistory);
+      else
+        dots(k_lb_dots<NC, false, false>, 0);
+    });
+  } else {
+    auto either = [&](auto both, auto alone) {
+      if (g)
+        dots(both, 2 * kMaxHistory);
+      else
+        dots(alone, 0);
+    };
+    if (cnt == 1)
+      either(k_lb_few_dots<1, true, true>, k_lb_few_dots<1, false, true>);
+    else if (cnt == 2)
+      either(k_lb_few_dots<2, true, true>, k_lb_few_dots<2, false, true>);
     else
-      hipLaunchKernelGGL((k_lb_dots<NC, false>), dim3(G), dim3(kLB), 0, st, h->n, h->tiles, h->S, R, y,
-                         (const double*)nullptr, h->P, kMaxHistory, 0);
-  });
+      either(k_lb_dots<2, true, true>, k_lb_dots<2, false, true>);
+  }
   if (!g)
     hipLaunchKernelGGL((k_lb_solve<true, 0>), dim3(1), dim3(kSolve), 0, st, h->P, (int64_t)G, R, 0,
                        h->SY, h->red);
