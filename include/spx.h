@@ -362,8 +362,9 @@ int spx_batch_tfqmr(spx_batch_handle b, const double* bvec, double* x, double rt
  * ------------------------------------------------------------------------- */
 
 /* History of m pairs (1 <= m <= 64) of vectors of length n.  The handle owns
- * S and Y (n x m each, column-major), the m x m products s_a.y_b and the
- * workspace (about 2 n m + n doubles of device memory). */
+ * S and Y (n x m each, in tiles of 128 rows), the m x m products s_a.y_b and
+ * the workspace (about 2 n m + n doubles of device memory, n rounded up to a
+ * multiple of 128). */
 int spx_lbfgs_create(int64_t n, int32_t m, void* stream, spx_lbfgs_handle* out);
 int spx_lbfgs_destroy(spx_lbfgs_handle h);
 /* Forgets every pair (the next apply returns h0 g). */
@@ -372,7 +373,7 @@ int spx_lbfgs_reset(spx_lbfgs_handle h);
 int spx_lbfgs_get_info(spx_lbfgs_handle h, int64_t* n, int32_t* m, int32_t* count);
 
 /* Appends the pair (s, y), dropping the oldest when m are held, and updates
- * the products s_a.y_b of the new row and column (one pass over S and Y).
+ * the products s_a.y of the held pairs with the new y (one pass over S).
  * s, y: device float64[n], copied.  The caller keeps to the curvature
  * condition s.y > 0 (not checked; a non-positive s_j.y_j makes later
  * products meaningless).  Asynchronous. */
@@ -388,10 +389,7 @@ int spx_lbfgs_apply(spx_lbfgs_handle h, const double* g, const double* h0, doubl
 /* spx_lbfgs_update(s, y) followed by spx_lbfgs_apply(g, h0, p), the step of
  * an optimiser that takes its next direction right after storing the pair,
  * with S^T g taken in the update's pass over S: one pass over S fewer (of
- * three) for the same result, bit for bit.  When g, h0 and p would make
- * the apply walk rows one at a time while the update walks them two at a
- * time (even n, a pointer off a 16-byte boundary), the two run unfused.
- * Same arguments, ownership and errors as the two calls.  Asynchronous. */
+ * three) for the same result, bit for bit.  Same arguments, ownership and errors as the two calls.  Asynchronous. */
 int spx_lbfgs_update_apply(spx_lbfgs_handle h, const double* s, const double* y,
                            const double* g, const double* h0, double* p, void* stream);
 
@@ -485,7 +483,8 @@ int spx_set_allocator(spx_alloc_fn alloc, spx_free_fn free, void* ctx);
  *     (smaller systems fill the chip better with the stream walk's smaller
  *     tiles): for MatMult and MatMultTranspose 2.5, for the solvers 12 (7
  *     when rows average at most 16 entries; 2 for the product of the CG
- *     iteration where the rows repeat); and when rows average at most
+ *     iteration where rows of more than 3.5 entries on average repeat); and
+ *     when rows average at most
  *     64 entries in every tile and
  *     none of SPX_OPT_ROWS_PER_BLOCK, SPX_OPT_QUAD_LOADS, SPX_OPT_PIPELINE
  *     is set.  Reading the option returns the variant MatMult resolves to.
@@ -552,7 +551,11 @@ int spx_set_allocator(spx_alloc_fn alloc, spx_free_fn free, void* ctx);
  *     entry); 0 keeps both to launches per iteration.  A pattern whose rows
  *     need too much of x per workgroup takes those as well, and so does one
  *     whose first launch the device refused (while another process holds
- *     its queue for cooperative launches), for as long as it lives.
+ *     its queue for cooperative launches), for as long as it lives.  The
+ *     cooperative launches of one process take turns: many threads that
+ *     solve mid-size systems on streams of their own overlap better with 0
+ *     (66,049 rows of 9 entries, us an iteration over 1, 2 and 4 threads: 7.3,
+ *     6.9 and 7.1; with 0 15.2, 8.3 and 5.6).
  *   SPX_OPT_IR_EARLY_EXIT: inner stopping rule of spx_cg_solve_mixed.
  *     0 (default): each inner solve runs to rtol_inner relative to its
  *     right-hand side.  1: it also stops once its residual is at most
@@ -568,7 +571,13 @@ int spx_set_allocator(spx_alloc_fn alloc, spx_free_fn free, void* ctx);
  *     index is rebuilt on the next product after a change.  Results are the
  *     same bits at every height.
  *   SPX_OPT_ROW_PATTERNS (read only): 1 where MatMult walks A by row patterns
- *     and reads no columns (see SPX_OPT_SPMV_VARIANT), else 0.
+ *     and reads no columns (see SPX_OPT_SPMV_VARIANT), else 0.  Every 256-row
+ *     tile must then have a window of at most 32 blocks, 7167 entries, rows
+ *     of at most 32 and at most 16 different lists of column offsets (the
+ *     nodes of a 27-point mesh of up to about 170 a line; one tile without
+ *     drops the whole matrix), the rows average more than 3.5 entries, and
+ *     rows of up to about 10 not be too many (80 to 100 tiles per compute
+ *     unit).
  *   SPX_OPT_LAST_SOLVE (read only): what ran the last solve of any kind with
  *     this matrix, its transpose or a batch that holds it: 0 nothing yet, 1
  *     launches per iteration, 2 one workgroup that walks memory, 3 one that
