@@ -728,6 +728,13 @@ unsigned pattern_blocks(int64_t tiles, int64_t limit = INT32_MAX) {
   return (unsigned)ceil_div(tiles, ceil_div(tiles, most));
 }
 
+// Rows that repeat and are long enough for the walk to pay, whatever the size:
+// up to 3 entries the lists take as many bytes as 16-bit columns (3 entries, 10^6 rows
+// 12.6 us a product and 11.1 by the window walk, the solvers' first kernel
+// 16.8 and 16.0 (in fp32 13.7 and 14.6); 1 entry, 4 x 10^6 rows 38 and 32, 49
+// and 38 (35 and 38); 4 entries 15.6 and 15.7).
+inline bool rows_repeat_enough(const Csr& A) { return A.win.patterned && 2 * A.nnz > 7 * A.n; }
+
 // Calls f with the form of the pattern walk that holds A's largest tile and
 // window, if there is one: 5, 9 and 27 entries a row are 3, 5 and 14 steps in
 // fp64, 2, 3 and 7 in fp32, with windows of 16 to 24 blocks on meshes of up
@@ -739,14 +746,6 @@ unsigned pattern_blocks(int64_t tiles, int64_t limit = INT32_MAX) {
 // blocks have none: 7 points, 252^3 rows (22 blocks) take 342 us by the
 // 14-step form and 257 by the window walk, the solvers' first kernel 357 and
 // 324 (and 183 in fp32, 207).
-//
-// rows_repeat_enough: rows long enough for that, whatever the size.  Up to 3
-// entries the lists take as many bytes as 16-bit columns: 3 entries, 10^6 rows
-// 12.6 us a product and 11.1 by the window walk, the solvers' first kernel
-// 16.8 and 16.0 (in fp32 13.7 and 14.6); 1 entry, 4 x 10^6 rows 38 and 32, 49
-// and 38 (35 and 38); 4 entries 15.6 and 15.7.
-inline bool rows_repeat_enough(const Csr& A) { return A.win.patterned && 2 * A.nnz > 7 * A.n; }
-
 template <typename VT, typename F>
 int with_pattern(const Csr& A, F&& f) {
   if (!A.win.patterned) return SPX_OK;
