@@ -322,11 +322,11 @@ int launch_spmm_pattern(const Csr& A, int64_t nrhs, const double* X, int64_t ldx
 // cg_grid.hip: a whole CG solve as one cooperative launch.  grid_cg_fits:
 // the pattern may take it.  launch_grid_cg: the fp64 solve, in the textbook
 // form or the single-reduction one, with the work vector u[n]; resets *st.
-// launch_grid_inner: the fp32 inner solve of the refinement, from the state k_ir_finish left in *st.  slots: kGridSlotWords
-// 8-byte words.  *launched is false when the device refused the launch (its
-// queue for cooperative launches serves one process at a time); asking costs
-// 40 ms then, so a pattern asks once.
-// Besides the solver's statuses st->status may come back as kGridUnfit
+// launch_grid_inner: the fp32 inner solve of the refinement, from the state
+// k_ir_finish left in *st.  slots: kGridSlotWords 8-byte words.  *launched is
+// false when the device refused the launch (its queue for cooperative
+// launches serves one process at a time); asking costs 40 ms then, so a
+// pattern asks once.  Besides the solver's statuses st->status may come back as kGridUnfit
 // (nothing solved, no vector changed), and st->verify as 1 when a wait
 // between workgroups gave up.
 constexpr int kGridSlotWords = 16384;

@@ -728,11 +728,11 @@ unsigned pattern_blocks(int64_t tiles, int64_t limit = INT32_MAX) {
   return (unsigned)ceil_div(tiles, ceil_div(tiles, most));
 }
 
-// Rows that repeat and are long enough for the walk to pay, whatever the size:
-// up to 3 entries the lists take as many bytes as 16-bit columns (3 entries, 10^6 rows
-// 12.6 us a product and 11.1 by the window walk, the solvers' first kernel
-// 16.8 and 16.0 (in fp32 13.7 and 14.6); 1 entry, 4 x 10^6 rows 38 and 32, 49
-// and 38 (35 and 38); 4 entries 15.6 and 15.7).
+// Rows that repeat and are long enough for the walk to pay, whatever the
+// size: up to 3 entries the lists take as many bytes as 16-bit columns (3
+// entries, 10^6 rows 12.6 us a product and 11.1 by the window walk, the
+// solvers' first kernel 16.8 and 16.0, in fp32 13.7 and 14.6; 1 entry, 4 x 10^6
+// rows 38 and 32, 49 and 38, 35 and 38; 4 entries 15.6 and 15.7).
 inline bool rows_repeat_enough(const Csr& A) { return A.win.patterned && 2 * A.nnz > 7 * A.n; }
 
 // Calls f with the form of the pattern walk that holds A's largest tile and
