@@ -1272,9 +1272,9 @@ int cg_solve_impl(spx_matrix* h, const Work& w, const Csr& M, const double* b, d
         h->last_solve.store(kCooperative, std::memory_order_relaxed);
         return rc;
       }
+      M.grid_unfit = true;  // the pattern's, kept with it: not tried again
       clear_error();
     }
-    M.grid_unfit = true;  // the pattern's, kept with it: not tried again
   }
   h->last_solve.store(form != 2 && use_one_workgroup(h, M) ? kOneWorkgroup : kByLaunches,
                       std::memory_order_relaxed);
@@ -1528,12 +1528,12 @@ extern "C" int spx_cg_solve_mixed(spx_handle h, const double* b, double* x, doub
           return set_error(SPX_HIP_ERROR,
                            "cg_solve_mixed: the workgroups of the resident solve lost step");
         if (fin.status == kGridUnfit) {
+          // the pattern's, kept with it; the launches below take this solve
+          M.grid_unfit32 = true;
           resident = false;
           hipLaunchKernelGGL(k_resume, dim3(1), dim3(64), 0, s, si);
         }
       }
-      // the pattern's, kept with it; the launches below take this solve
-      if (!resident) M.grid_unfit32 = true;
     }
     h->last_solve.store(resident ? kCooperative : kByLaunches, std::memory_order_relaxed);
     if (!resident)

@@ -657,6 +657,15 @@ int grid_launch(const GridPlan& g, const void* fn, GridMat<VT>& A, Args& a, CgSc
   return SPX_OK;
 }
 
+// Whether a refused launch says something about the device, and not only that
+// s is being captured.
+bool refused_for_good(hipStream_t s) {
+  hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+  const bool known = hipStreamIsCapturing(s, &c) == hipSuccess;
+  (void)hipGetLastError();
+  return known && c == hipStreamCaptureStatusNone;
+}
+
 }  // namespace
 
 bool grid_cg_fits(const Csr& M, bool fp32) {
@@ -680,7 +689,9 @@ int launch_grid_cg(const Csr& M, bool textbook, const double* b, double* x, doub
                         : reinterpret_cast<const void*>(&k_cg_grid<kGridMaxRpt, T>);
   };
   const void* fn = textbook ? form(std::true_type()) : form(std::false_type());
-  return grid_launch(g, fn, A, a, st, maxit, s, launched);
+  SPX_TRY(grid_launch(g, fn, A, a, st, maxit, s, launched));
+  if (!*launched && refused_for_good(s)) M.grid_unfit = true;
+  return SPX_OK;
 }
 
 int launch_grid_inner(const Csr& M, float* x, const float* r, float* z, const float* dinv,
@@ -693,7 +704,9 @@ int launch_grid_inner(const Csr& M, float* x, const float* r, float* z, const fl
   const void* fn = g.rpt == 1   ? reinterpret_cast<const void*>(&k_cg_grid_inner<1>)
                    : g.rpt == 2 ? reinterpret_cast<const void*>(&k_cg_grid_inner<2>)
                                 : reinterpret_cast<const void*>(&k_cg_grid_inner<kGridMaxRpt>);
-  return grid_launch(g, fn, A, a, (CgScalars*)nullptr, 0, s, launched);
+  SPX_TRY(grid_launch(g, fn, A, a, (CgScalars*)nullptr, 0, s, launched));
+  if (!*launched && refused_for_good(s)) M.grid_unfit32 = true;
+  return SPX_OK;
 }
 
 }  // namespace spx

@@ -325,8 +325,8 @@ int launch_spmm_pattern(const Csr& A, int64_t nrhs, const double* X, int64_t ldx
 // launch_grid_inner: the fp32 inner solve of the refinement, from the state
 // k_ir_finish left in *st.  slots: kGridSlotWords 8-byte words.  *launched is
 // false when the device refused the launch (its queue for cooperative
-// launches serves one process at a time); asking costs 40 ms then, so a
-// pattern asks once.  Besides the solver's statuses st->status may come back as kGridUnfit
+// launches serves one process at a time); asking costs 40 ms then, so it is
+// noted in the pattern and not tried again.  Besides the solver's statuses st->status may come back as kGridUnfit
 // (nothing solved, no vector changed), and st->verify as 1 when a wait
 // between workgroups gave up.
 constexpr int kGridSlotWords = 16384;
