@@ -55,7 +55,7 @@ __device__ __forceinline__ int32_t wg_max(int32_t v, int32_t* red) {
 // given up.  *nopat is set where a tile with a window has no patterns, and no
 // further tile looks for any; one without a window shows in stats[0] (a store
 // to one address by each of them took 1.2 ms instead of 0.24 on 5M rows of
-// random columns).
+// random columns).  No patterns are looked for without row.
 __global__ __launch_bounds__(kWinRows) void k_win_tiles(int64_t n, const int32_t* __restrict__ rowptr,
                                                         const int32_t* __restrict__ col,
                                                         const uint32_t* __restrict__ off,
@@ -82,7 +82,7 @@ __global__ __launch_bounds__(kWinRows) void k_win_tiles(int64_t n, const int32_t
   const int tid = threadIdx.x;
   if (t0 == t1) {
     if (tid == 0) cnt[t] = 0;
-    if (tid < r1 - r0) row[r0 + tid] = 0;
+    if (row && tid < r1 - r0) row[r0 + tid] = 0;
     return;
   }
   int32_t lo = INT_MAX, hi = -1;
@@ -136,7 +136,7 @@ __global__ __launch_bounds__(kWinRows) void k_win_tiles(int64_t n, const int32_t
   if (c == 0) return;
   const int32_t rs = tid < r1 - r0 ? rowptr[r0 + tid] - t0 : 0;
   const int32_t len = tid < r1 - r0 ? rowptr[r0 + tid + 1] - t0 - rs : 0;
-  const bool fit = __syncthreads_and(len <= kPatLen);
+  const bool fit = __syncthreads_and(len <= kPatLen) && row;
   uint32_t rank = incl[tid] - __popc(word);
   for (uint32_t m = word; m != 0; m &= m - 1)
     list[t * kWinMaxBlocks + rank++] = lo + tid * 32 + (__ffs(m) - 1);
@@ -150,6 +150,7 @@ __global__ __launch_bounds__(kWinRows) void k_win_tiles(int64_t n, const int32_t
     lcol[e] = v;
     if (fit) lc[e - t0] = v;
   }
+  if (!row) return;
   __shared__ uint32_t quit;
   if (tid == 0)
     quit = __hip_atomic_load(nopat, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) |
@@ -215,9 +216,11 @@ int window_enqueue(const Csr& A, int64_t most, const uint32_t* off, uint32_t* sc
   *w = Window();
   if (A.n == 0 || most == 0) return SPX_OK;
   const int64_t tiles = ceil_div(A.n, kWinRows), cap = most_blocks(most);
+  // products walk by patterns from 1.5 entries a row on; they are 8 bytes a row
+  const bool patterns = 2 * most > 3 * A.n;
   const int64_t words = tiles + 1 + cap, row = (words + 15) & ~int64_t(15);
-  const int64_t pat = (row + A.n + 15) & ~int64_t(15);
-  const int64_t lcol = pat + tiles * (kPats * kPatLen / 2);
+  const int64_t pat = patterns ? (row + A.n + 15) & ~int64_t(15) : row;
+  const int64_t lcol = patterns ? pat + tiles * (kPats * kPatLen / 2) : row;
   int32_t* block = nullptr;
   const int st = dalloc(reinterpret_cast<void**>(&block),
                         (size_t)(lcol * 4 + most * (int64_t)sizeof(uint16_t) + 128));
@@ -229,8 +232,8 @@ int window_enqueue(const Csr& A, int64_t most, const uint32_t* off, uint32_t* sc
   w->block = block;
   w->ptr = block;
   w->blk = block + tiles + 1;
-  w->row = reinterpret_cast<uint32_t*>(block + row);
-  w->pat = reinterpret_cast<uint16_t*>(block + pat);
+  w->row = patterns ? reinterpret_cast<uint32_t*>(block + row) : nullptr;
+  w->pat = patterns ? reinterpret_cast<uint16_t*>(block + pat) : nullptr;
   w->lcol = reinterpret_cast<uint16_t*>(block + lcol);
   uint32_t* cnt = scratch;
   int32_t* list = reinterpret_cast<int32_t*>(scratch + tiles);
@@ -264,7 +267,7 @@ void window_keep(Csr& A, const uint32_t* stats, Window* w) {
     A.win.max_blocks = largest;
     A.win.total_blocks = total;
     A.win.gather_entries = gather;
-    A.win.patterned = stats[5] == 0 && gather == 0;
+    A.win.patterned = w->row && stats[5] == 0 && gather == 0;
     *w = Window();
   } else {
     window_release(w);
